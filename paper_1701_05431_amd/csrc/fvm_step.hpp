@@ -460,12 +460,29 @@ __device__ inline void finalize_grid(GridScratch* s, const GridGeom& g, double d
     s->nstep = n + 1;
   }
   if (dt_out) *dt_out = dtn;
-  __threadfence();
   atomicExch(&s->arrive, 0u);
 }
 
+// The two values have come back: what follows in program order is issued
+// after the operations that return them have been performed.
+__device__ __forceinline__ void returned(unsigned long long x, unsigned long long y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : : "v"(x), "v"(y) : "memory");
+#else
+  (void)x;
+  (void)y;
+#endif
+}
+
 // Workgroup max of (bx, by); thread 0 commits it and returns true if its
-// workgroup is the last of `total` arrivals on s.
+// workgroup is the last of `total` arrivals on s. The maxima come back before
+// the arrival is issued, and all of these act at the device's point of
+// coherence, so the last workgroup reads every maximum. No fence: the cells
+// are read by later launches only, and a device-scope fence writes the XCD's
+// whole L2 back, once per workgroup (with it, 20 steps of 256 grids took
+// 29.3 ms instead of 21.1, of the 1531 x 997 grid 1.23 instead of 1.07, of the
+// 2048^2 spray 2.38 instead of 2.25, of the 4096^2 Euler grid 4.75 instead of
+// 4.61).
 template <int WPB>
 __device__ __forceinline__ bool block_commit(unsigned long long bx, unsigned long long by,
                                              GridScratch* s, unsigned int total) {
@@ -486,9 +503,9 @@ __device__ __forceinline__ bool block_commit(unsigned long long bx, unsigned lon
       mx = umax64(mx, red[0][k]);
       my = umax64(my, red[1][k]);
     }
-    atomicMax(&s->smax[0], mx);
-    atomicMax(&s->smax[1], my);
-    __threadfence();
+    const unsigned long long ox = atomicMax(&s->smax[0], mx);
+    const unsigned long long oy = atomicMax(&s->smax[1], my);
+    returned(ox, oy);
     const unsigned int t = atomicAdd(&s->arrive, 1u);
     last = (t == total - 1);
   }
