@@ -8,12 +8,17 @@
 // n(S) = exp(l0 + l1 x + l2 x^2 + l3 x^3) on S in [0, 1]; its multipliers
 // minimise the convex dual Phi(l) = int n dS - sum_k l_k m_{k/2}, whose
 // gradient is the moment mismatch and whose Hessian is the 4 x 4 matrix of
-// the moments m_{(k+l)/2}. Each cell runs Newton's method on Phi from the
-// normal density in x with the cell's mean and variance of x, or from the
-// cell's multipliers of the previous pass when the caller keeps them (steps
-// cut back until Phi decreases while the mismatch is large), with every moment
-// integral taken by a composite 8-point Gauss-Legendre rule over 16 panels of
-// x. Then n(S=0) = exp(l0) and m_{-1/2} = int S^{-1/2} n dS.
+// the moments m_{(k+l)/2}, and n(S=0) = exp(l0), m_{-1/2} = int S^{-1/2} n dS.
+//
+// A wave solves its 64 cells together (fvm_entropy.hpp). Cells outside that
+// solver's range (size distributions with their mass at an end of [0, 1], or
+// narrower than its quadrature rules resolve) and cells it does not bring to
+// convergence are solved one by one by the general solver here: Newton's method
+// on Phi from the normal density in x with the cell's mean and variance of x,
+// or from the cell's multipliers of the previous pass when the caller keeps
+// them (steps cut back until Phi decreases while the mismatch is large), with
+// every moment integral taken by a composite 8-point Gauss-Legendre rule over
+// 16 panels of x; it decides which moments cannot be matched at all.
 //
 // The pass runs after the transport-only step kernel: per cell it reads W*
 // and the gas velocity, writes W^{n+1} = W* + dt S(W*) in place, and reduces
@@ -30,6 +35,7 @@
 #include <cstdint>
 
 #include "fvm_adjoint_spray.hpp"
+#include "fvm_entropy.hpp"
 #include "fvm_host.hpp"
 #include "fvm_internal.hpp"
 #include "fvm_models.hpp"
@@ -37,19 +43,10 @@
 
 namespace fvm {
 
-// Quadrature nodes evaluated per unrolled loop step, and the minimum number
-// of waves per SIMD the source pass is compiled for (0: the compiler's
-// choice).
-#ifndef FVM_MAXENT_UNROLL
-#define FVM_MAXENT_UNROLL 8
-#endif
-#ifndef FVM_MAXENT_WAVES
-#define FVM_MAXENT_WAVES 0
-#endif
-
 constexpr int kMePanels = 16;
 constexpr int kMeThreads = 256;
-constexpr int kMeMaxBlocks = 8192;
+// one resident set: two workgroups of four waves per CU
+constexpr int kMeMaxBlocks = 512;
 
 // m[j] = int S^{(j-1)/2} n dS = 2 int x^j e^{p(x)} dx for j = 0..7: m[0] is
 // m_{-1/2}, m[1..4] the model's moments, m[5..7] the higher ones the Hessian
@@ -59,7 +56,7 @@ __device__ __forceinline__ void me_moments(const double* l, const MaxEntRule& r,
   for (int j = 0; j < 8; ++j) m[j] = 0.0;
   constexpr double h = 1.0 / kMePanels;
   for (int p = 0; p < kMePanels; ++p) {
-#pragma unroll FVM_MAXENT_UNROLL
+#pragma unroll 2
     for (int q = 0; q < 8; ++q) {
       const double x = fma(r.x[q], h, p * h);
       const double poly = fma(fma(fma(l[3], x, l[2]), x, l[1]), x, l[0]);
@@ -177,7 +174,7 @@ __device__ bool maxent_newton(const double* w, const MaxEntRule& r, double* l, d
 // ones); otherwise, or if that fails, from the normal density in x with the
 // cell's mean and variance of x. l returns the converged multipliers. False
 // if the moments cannot be matched.
-__device__ bool maxent_closure(const double* w, const MaxEntRule& r, bool warm, double* l,
+__device__ __attribute__((noinline)) bool maxent_closure(const double* w, const MaxEntRule& r, bool warm, double* l,
                                double& mmh, double& n0) {
   if (warm && finite(l[0]) && finite(l[1]) && finite(l[2]) && finite(l[3])) {
     double t[4] = {l[0], l[1], l[2], l[3]};
@@ -200,14 +197,51 @@ __device__ bool maxent_closure(const double* w, const MaxEntRule& r, bool warm, 
   return true;
 }
 
-#if FVM_MAXENT_WAVES > 0
-#define FVM_MAXENT_ATTR __attribute__((amdgpu_waves_per_eu(FVM_MAXENT_WAVES)))
-#else
-#define FVM_MAXENT_ATTR
-#endif
+// The cell of one lane: the wave takes 64 consecutive cells (row-major).
+// One 64-bit division per wave; a lane's own is 32 bits wide.
+struct LaneCell {
+  bool in;
+  int j, i;
+};
+__device__ __forceinline__ LaneCell lane_cell(const GridGeom& g, long long base, long long ncell) {
+  const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+  const int jb = static_cast<int>(base / g.nx), ib = static_cast<int>(base % g.nx);
+  const unsigned i = static_cast<unsigned>(ib) + static_cast<unsigned>(lane);
+  const unsigned down = i / static_cast<unsigned>(g.nx);
+  LaneCell c;
+  c.in = base + lane < ncell;
+  c.j = c.in ? jb + static_cast<int>(down) : 0;
+  c.i = c.in ? static_cast<int>(i - down * static_cast<unsigned>(g.nx)) : 0;
+  return c;
+}
+__device__ __forceinline__ long long wave_base() {
+  return (static_cast<long long>(blockIdx.x) * (kMeThreads / kWave) + wave_index()) * kWave;
+}
 
-__global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_source_kernel(
-    StepArgs a, MaxEntRule r, MaxEntWarm wm) {
+// The closure of a wave's cells: entropy::solve for all of them together,
+// then the general solver above for the lanes it leaves. `l` in and out:
+// multipliers in powers of x (in: the start, if warm).
+__device__ __forceinline__ bool wave_closure(bool live, const double* w, const MaxEntRule& r,
+                                             bool warm, double* l, double& mmh, double& n0,
+                                             entropy::Result& e) {
+  double c[4];
+  entropy::from_x(l, c);
+  e = entropy::solve(live, w, warm, c);
+  bool ok = e.ok;
+  mmh = e.mmh;
+  n0 = e.n0;
+  if (live && !e.ok) {
+    ok = maxent_closure(w, r, warm, l, mmh, n0);
+  } else if (live) {
+    entropy::to_x(e.c, l);
+  }
+  return ok;
+}
+
+// Two waves per SIMD (247 registers): held to 168 or 128 registers for three
+// or four, the solver's state spills and 1024^2 cells take 10 and 17 % longer.
+__global__ __launch_bounds__(kMeThreads, 2) void maxent_source_kernel(StepArgs a, MaxEntRule r,
+                                                                      MaxEntWarm wm) {
   const Spray m(a.m);
   bool cfl_fail;
   const double dt = launch_dt(a, cfl_fail);
@@ -215,33 +249,38 @@ __global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_source_kern
   const double K = a.m.K, inv_theta = a.m.inv_theta;
   unsigned long long bx = 0, by = 0;
   const long long ncell = static_cast<long long>(a.g.nx) * a.g.ny;
-  for (long long c = static_cast<long long>(blockIdx.x) * kMeThreads + threadIdx.x; c < ncell;
-       c += static_cast<long long>(kMeThreads) * gridDim.x) {
-    const int j = static_cast<int>(c / a.g.nx), i = static_cast<int>(c % a.g.nx);
-    double* cell = a.wout + static_cast<size_t>(j) * a.g.ld + i;
+  const size_t lp = static_cast<size_t>(ncell);
+  for (long long base = wave_base(); base < ncell;
+       base += static_cast<long long>(kMeThreads) * gridDim.x) {
+    const LaneCell at = lane_cell(a.g, base, ncell);
+    double* cell = a.wout + static_cast<size_t>(at.j) * a.g.ld + at.i;
     double w[6];
 #pragma unroll
     for (int v = 0; v < 6; ++v) w[v] = cell[v * a.g.plane];
     const double m0 = w[0], m1 = w[1], m2 = w[2];
     // dt = 0 (a failed CFL check, a dry run) leaves the state as it is
-    if (dte != 0.0 && m0 > 1e-300 && m1 > 1e-300 && m2 > 1e-300) {
-      const size_t uc = ucell(a.g, j, i);
-      const double ugx = a.ug[uc], ugy = a.ug[a.g.uplane + uc];
-      // K = 0: no evaporation, and the closure is not needed
-      double mmh = 0.0, n0 = 0.0;
-      const size_t lc = static_cast<size_t>(j) * a.g.nx + i;
-      const size_t lp = static_cast<size_t>(a.g.nx) * a.g.ny;
+    const bool live = at.in && dte != 0.0 && m0 > 1e-300 && m1 > 1e-300 && m2 > 1e-300;
+    // K = 0: no evaporation, and the closure is not needed
+    double mmh = 0.0, n0 = 0.0;
+    bool ok = true;
+    if (K != 0.0) {
+      const size_t lc = static_cast<size_t>(base) + (threadIdx.x & (kWave - 1));
       double l[4] = {0.0, 0.0, 0.0, 0.0};
-      if (wm.lam && wm.warm) {
+      if (wm.lam && wm.warm && live) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) l[k] = wm.lam[k * lp + lc];
       }
-      const bool ok = K == 0.0 || maxent_closure(w, r, wm.warm != 0, l, mmh, n0);
-      if (ok && K != 0.0 && wm.lam) {
+      entropy::Result e;
+      ok = wave_closure(live, w, r, wm.warm != 0, l, mmh, n0, e);
+      if (ok && live && wm.lam) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) wm.lam[k * lp + lc] = l[k];
       }
+    }
+    if (live) {
       if (ok) {
+        const size_t uc = ucell(a.g, at.j, at.i);
+        const double ugx = a.ug[uc], ugy = a.ug[a.g.uplane + uc];
         const double r2 = 1.0 / m2;
         const double ux = w[4] * r2, uy = w[5] * r2;
         const double Km0 = K * m0;
@@ -258,10 +297,12 @@ __global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_source_kern
 #pragma unroll
       for (int v = 0; v < 6; ++v) cell[v * a.g.plane] = w[v];
     }
-    double sx, sy;
-    m.speeds(w, sx, sy);
-    bx = umax64(bx, bits(sx));
-    by = umax64(by, bits(sy));
+    if (at.in) {
+      double sx, sy;
+      m.speeds(w, sx, sy);
+      bx = umax64(bx, bits(sx));
+      by = umax64(by, bits(sy));
+    }
   }
   if (block_commit<kMeThreads / kWave>(bx, by, a.scr, gridDim.x) && threadIdx.x == 0) {
     if (cfl_fail) atomicOr(&a.scr->status, kStatusCfl);
@@ -281,15 +322,16 @@ __global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_source_kern
 // and the transposed rows are H^{-1} (-K lam_0 dn0/dl - K/2 lam_1 dm_{-1/2}/dl)
 // (H is symmetric). Newton starts cold in every cell. A cell whose moments the
 // closure cannot match gets NaN multipliers.
-__global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_adjoint_source_kernel(
-    AdjointArgs a, const double* ug, MaxEntRule r) {
+__global__ __launch_bounds__(kMeThreads, 2) void maxent_adjoint_source_kernel(AdjointArgs a,
+                                                                              const double* ug,
+                                                                              MaxEntRule r) {
   const double dt = a.dts ? a.dts[a.k] : a.dt_arg;
   const double K = a.m.K, it = a.m.inv_theta;
   const long long ncell = static_cast<long long>(a.g.nx) * a.g.ny;
-  for (long long c = static_cast<long long>(blockIdx.x) * kMeThreads + threadIdx.x; c < ncell;
-       c += static_cast<long long>(kMeThreads) * gridDim.x) {
-    const int j = static_cast<int>(c / a.g.nx), i = static_cast<int>(c % a.g.nx);
-    const size_t at = static_cast<size_t>(j) * a.g.ld + i;
+  for (long long base = wave_base(); base < ncell;
+       base += static_cast<long long>(kMeThreads) * gridDim.x) {
+    const LaneCell lc = lane_cell(a.g, base, ncell);
+    const size_t at = static_cast<size_t>(lc.j) * a.g.ld + lc.i;
     double ws[6], lam[6], mu[6];
 #pragma unroll
     for (int v = 0; v < 6; ++v) {
@@ -297,31 +339,71 @@ __global__ __launch_bounds__(kMeThreads) FVM_MAXENT_ATTR void maxent_adjoint_sou
       lam[v] = a.lam_in[v * a.g.plane + at];
       mu[v] = lam[v];
     }
-    if (ws[0] > sadj::kVac && ws[1] > sadj::kVac && ws[2] > sadj::kVac) {
-      const size_t uc = ucell(a.g, j, i);
+    const bool live = lc.in && ws[0] > sadj::kVac && ws[1] > sadj::kVac && ws[2] > sadj::kVac;
+    double y[4] = {0.0, 0.0, 0.0, 0.0};
+    if (K != 0.0) {  // uniform: every lane takes part in the closure
+      double l[4] = {0.0, 0.0, 0.0, 0.0}, mmh, n0;
+      entropy::Result e;
+      bool ok = wave_closure(live, ws, r, false, l, mmh, n0, e);
+      // the moments at the converged multipliers, by the finest rule any lane
+      // needs
+      const bool quick = live && e.ok;
+      if (__any(quick)) {
+        double P[entropy::kMoments], N[7];
+        double c[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = quick ? e.c[k] : 0.0;
+        int rule = 0;
+        const int want = quick ? entropy::rule_of(entropy::curvature(c, -1.0, 1.0)) : 0;
+#pragma unroll
+        for (int k = 1; k < entropy::kRuleCount; ++k) rule = __any(want >= k) ? k : rule;
+        entropy::moments(c, rule, P);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) N[k] = 0.5 * (P[k] + P[k + 1]);
+        const entropy::Hankel H(N);
+        // H y = rhs in powers of t (x^k at S = 0 is (-1)^k there, and
+        // int S^{-1/2} t^k n dS = P_k), then to powers of x
+        const double ra = -K * lam[0] * n0, rb = -0.5 * K * lam[1];
+        const double g[4] = {fma(rb, P[0], ra), fma(rb, P[1], -ra), fma(rb, P[2], ra),
+                             fma(rb, P[3], -ra)};
+        double z[4];
+        H.solve(g, z);
+        if (quick) {
+          ok = ok && H.ok;
+          y[0] = z[0] - z[1] + z[2] - z[3];
+          y[1] = fma(6.0, z[3], fma(-4.0, z[2], 2.0 * z[1]));
+          y[2] = fma(-12.0, z[3], 4.0 * z[2]);
+          y[3] = 8.0 * z[3];
+        }
+      }
+      if (live && !e.ok && ok) {
+        double m[8], ya[4], yb[4];
+        me_moments(l, r, m);
+        // H y = rhs through the Newton direction solver (H d = -g)
+        const double ra[4] = {K * lam[0] * n0, 0.0, 0.0, 0.0};
+        const double rb[4] = {0.5 * K * lam[1] * m[0], 0.5 * K * lam[1] * m[1],
+                              0.5 * K * lam[1] * m[2], 0.5 * K * lam[1] * m[3]};
+        ok = me_direction(m, ra, ya) && me_direction(m, rb, yb);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = ya[k] + yb[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = ok ? y[k] : __builtin_nan("");
+    }
+    if (live) {
+      const size_t uc = ucell(a.g, lc.j, lc.i);
       const double ugc[2] = {ug[uc], ug[a.g.uplane + uc]};
       double g[6];
       sadj::SprayAdj::source_rows(ws, lam, ugc, K, it, 1.0 / ws[2], g);
-      if (K != 0.0) {
-        double l[4] = {0.0, 0.0, 0.0, 0.0}, mmh, n0, m[8];
-        bool ok = maxent_closure(ws, r, false, l, mmh, n0);
-        double ya[4], yb[4];
-        if (ok) {
-          me_moments(l, r, m);
-          // H y = rhs through the Newton direction solver (H d = -g)
-          const double ra[4] = {K * lam[0] * n0, 0.0, 0.0, 0.0};
-          const double rb[4] = {0.5 * K * lam[1] * m[0], 0.5 * K * lam[1] * m[1],
-                                0.5 * K * lam[1] * m[2], 0.5 * K * lam[1] * m[3]};
-          ok = me_direction(m, ra, ya) && me_direction(m, rb, yb);
-        }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) g[k] += ok ? ya[k] + yb[k] : __builtin_nan("");
-      }
+      for (int k = 0; k < 4; ++k) g[k] += y[k];
 #pragma unroll
       for (int v = 0; v < 6; ++v) mu[v] = fma(dt, g[v], mu[v]);
     }
+    if (lc.in) {
 #pragma unroll
-    for (int v = 0; v < 6; ++v) a.lam_out[v * a.g.plane + at] = mu[v];
+      for (int v = 0; v < 6; ++v) a.lam_out[v * a.g.plane + at] = mu[v];
+    }
   }
 }
 
