@@ -113,7 +113,9 @@ int fvm_nvar(int model);
 int fvm_validate(const fvm_params* p);
 
 /* Bytes of device scratch a grid needs (speed maxima, arrival counter, time
- * step, status word); a multiple of 256. */
+ * step, status word: 256 bytes; and for a grid that fits on the chip, see
+ * fvm_set_resident_runs, the words its tiles exchange during a run, up to
+ * 10 MB); a multiple of 256. */
 size_t fvm_scratch_bytes(const fvm_params* p);
 
 /* ---- single grid ------------------------------------------------------- */
@@ -330,16 +332,26 @@ int fvm_set_adjoint_tiling(fvm_grid* g, int rows_per_strip, int waves_per_block,
 int fvm_set_cells_per_lane(fvm_grid* g, int cells_per_lane);
 int fvm_get_cells_per_lane(const fvm_grid* g);
 
-/* Resident runs: fvm_run on a grid whose two states fit in one workgroup's
- * LDS (2 x nVar x nx x ny <= 18432 doubles, e.g. advection up to 96 x 96,
- * Euler up to 48 x 48; no halo rows; the spray with the lognormal closure
- * only) executes all its adaptive steps (Sec. 2.2.1 eq. VF_scheme and
- * eq. CFL_cond, one dt per step) in one launch of one workgroup, which keeps
- * the state in LDS between steps, instead of one launch per step. States,
- * dts, the dt log, the maxima and the status are bitwise those of the step
- * launches; the other ping-pong buffer ends up holding the state before the
- * last step, as with step launches. enable != 0 (the default) allows it,
- * 0 forces step launches. FVM_EINVAL for a NULL grid. */
+/* Resident runs. A grid that fits on the chip keeps its state there for a
+ * whole run, in one launch, instead of one launch per step (Sec. 2.2.1
+ * eq. VF_scheme and eq. CFL_cond; no halo rows; the spray with the lognormal
+ * closure only):
+ *  - fvm_run on a grid whose two states fit in one workgroup's LDS
+ *    (2 x nVar x nx x ny <= 18432 doubles, e.g. advection up to 96 x 96, Euler
+ *    up to 48 x 48) runs in one workgroup;
+ *  - fvm_run, fvm_run_fixed, fvm_run_dts, fvm_run_ckpt and the recomputation
+ *    of fvm_adjoint_run on a grid that up to 256 tiles of 62 columns and 300
+ *    (advection), 76 (Euler) or 50 (spray) rows cover, e.g. 1024 x 1024 Euler,
+ *    run on up to 256 workgroups that exchange their tiles' edges, unless the
+ *    caller has chosen a strip shape (fvm_set_tiling, fvm_set_cells_per_lane) or
+ *    the stream is being captured. Such runs wait for each other across the
+ *    streams of a process; should the workgroups not all become resident (the
+ *    device is shared with another process's), one workgroup makes the run.
+ * States, dts, the dt log, the maxima and the status are bitwise those of
+ * the step launches; the other ping-pong buffer ends up holding the state
+ * before the last step, as with step launches (fvm_run, fvm_run_fixed,
+ * fvm_run_dts). enable != 0 (the default) allows it, 0 forces step launches.
+ * FVM_EINVAL for a NULL grid. */
 int fvm_set_resident_runs(fvm_grid* g, int enable);
 
 /* Autotuner: picks the tiling and lane layout of the fused step by timing

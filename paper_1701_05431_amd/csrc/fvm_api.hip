@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/fvm.h"
+#include "fvm_cluster.hpp"
 #include "fvm_host.hpp"
 #include "fvm_internal.hpp"
 
@@ -33,6 +34,10 @@ hipError_t launch_adjoint(const AdjointArgs& a, int model, const double* ug, hip
 hipError_t launch_spray_adjoint(const AdjointArgs& a, const double* ug, hipStream_t st,
                                 bool src);
 hipError_t launch_maxent_adjoint_source(const AdjointArgs& a, const double* ug, hipStream_t st);
+namespace cluster {
+hipError_t launch_clear_area(u64* area, size_t words, hipStream_t st);
+hipError_t launch_run(const Args& a, int model, hipStream_t st);
+}  // namespace cluster
 
 GridGeom grid_geometry(const fvm_params& p) {
   GridGeom g{};
@@ -173,10 +178,49 @@ bool valid_tiling(int rows, int wpb) {
 int dev_err(hipError_t e) { return e == hipSuccess ? FVM_OK : FVM_EDEVICE; }
 
 int status_from_bits(unsigned int st) {
+  if (st & kStatusWait) return FVM_EDEVICE;
   if (st & kStatusNonFinite) return FVM_ENONFINITE;
   if (st & kStatusCfl) return FVM_ECFL;
   if (st & kStatusDt) return FVM_EINVAL;
   return FVM_OK;
+}
+
+// The tiles of a run that keeps the state on the chip; false where the grid
+// does not fit or its step is not one kernel (entropy closure).
+bool cluster_plan(const fvm_params& p, cluster::Plan* plan) {
+  return p.closure == FVM_CLOSURE_LOGNORMAL &&
+         cluster::make_plan(fvm_nvar(p.model), p.nx, p.ny, plan);
+}
+size_t cluster_bytes(const fvm_params& p) {
+  cluster::Plan plan;
+  if (!cluster_plan(p, &plan)) return 0;
+  return (sizeof(cluster::u64) * cluster::area_words(fvm_nvar(p.model), plan) + 255) / 256 * 256;
+}
+
+// Two such runs at once, from two streams, could each hold some of the CUs
+// and wait for the rest; the second waits for the first instead. One event
+// per device, kept until the process ends.
+struct ClusterTurn {
+  std::mutex mu;
+  hipEvent_t ended = nullptr;
+  hipStream_t stream = nullptr;
+};
+constexpr int kTurnDevices = 64;
+ClusterTurn g_turn[kTurnDevices];
+
+hipError_t launch_in_turn(const cluster::Args& a, int model, int device, hipStream_t st) {
+  ClusterTurn& t = g_turn[device];
+  std::lock_guard<std::mutex> lock(t.mu);
+  hipError_t e = hipSuccess;
+  if (!t.ended) {
+    e = hipEventCreateWithFlags(&t.ended, hipEventDisableTiming);
+  } else if (t.stream != st) {
+    e = hipStreamWaitEvent(st, t.ended, 0);
+  }
+  if (e == hipSuccess) e = cluster::launch_run(a, model, st);
+  if (e == hipSuccess) e = hipEventRecord(t.ended, st);
+  t.stream = st;
+  return e;
 }
 
 struct GraphKey {
@@ -214,7 +258,11 @@ struct fvm_grid {
   int adj_rows = kDefaultRows, adj_wpb = kDefaultWpb;  // adjoint kernel tile shape
   int adj_cpl = 1;   // adjoint cells per lane (the tuner may pick 2 where allowed)
   int cpl_req = 0;   // requested cells per lane (0: the widest the buffers allow)
-  bool resident = true;  // small grids run whole adaptive runs in one workgroup
+  bool resident = true;  // grids that fit on the chip keep the state there for a whole run
+  cluster::Plan plan{};  // .. their tiles, and whether there are any
+  bool plan_ok = false;
+  bool strips_asked = false;  // the caller chose a strip shape: its runs are step launches
+  int device = -1;
   int cpl = 1;       // layout in use
   double* w_a = nullptr;
   double* w_b = nullptr;
@@ -225,6 +273,7 @@ struct fvm_grid {
   double* me_lam = nullptr;        // entropy closure: the caller's multiplier buffer
   bool me_valid = false;           // it holds the multipliers of the current state's cells
   GridScratch* scr = nullptr;
+  cluster::u64* area() const { return reinterpret_cast<cluster::u64*>(scr + 1); }
   const double* log_armed = nullptr;  // dt log the scratch currently points to
   hipStream_t stream = nullptr;
   bool bound = false;
@@ -288,7 +337,7 @@ int fvm_validate(const fvm_params* p) { return valid_params(p) ? FVM_OK : FVM_EI
 
 size_t fvm_scratch_bytes(const fvm_params* p) {
   if (!valid_params(p)) return 0;
-  return sizeof(GridScratch);
+  return sizeof(GridScratch) + cluster_bytes(*p);
 }
 
 int fvm_create(const fvm_params* p, fvm_grid** out) {
@@ -304,6 +353,7 @@ int fvm_create(const fvm_params* p, fvm_grid** out) {
   default_tiling(*p, 1, &g->adj_rows, &g->adj_wpb);
   g->g = grid_geometry(*p);
   g->m = model_consts(*p);
+  g->plan_ok = cluster_plan(*p, &g->plan);
   *out = g;
   return FVM_OK;
 }
@@ -356,6 +406,16 @@ int fvm_bind(fvm_grid* g, double* w_a, double* w_b, const double* ug, void* scra
   g->speeds_valid = false;
   g->me_valid = false;
   g->log_armed = nullptr;
+  if (g->plan_ok) {  // one workgroup of a run per CU, all of them at once
+    int cus = 0;
+    if (hipGetDevice(&g->device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess)
+      return FVM_EDEVICE;
+    if (g->device >= kTurnDevices || cus < g->plan.tiles) g->device = -1;
+    const int rc = dev_err(cluster::launch_clear_area(
+        g->area(), cluster::area_words(g->nv, g->plan), g->stream));
+    if (rc) return rc;
+  }
   return dev_err(launch_clear_scratch(g->scr, 1, g->stream));
 }
 
@@ -673,6 +733,37 @@ static bool resident_ok(const fvm_grid* g) {
   return need <= kResidentDoubles;
 }
 
+// A run of steps can keep the state in the LDS of all CUs: the grid fits, no
+// halo rows, the caller has not asked for a strip shape, and the stream is not
+// being captured (the launch may have to wait for another stream's).
+static bool cluster_ok(const fvm_grid* g) {
+  if (!g->resident || !g->plan_ok || g->device < 0 || g->strips_asked || g->halo.s || g->halo.n)
+    return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(g->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+}
+
+// nsteps steps from state `win` kept on the chip: the last state goes to
+// w_last, the one before it to w_prev (either may be null).
+static cluster::Args cluster_args(const fvm_grid* g, int mode, int nsteps, const double* win,
+                                  double* w_last, double* w_prev) {
+  cluster::Args a{};
+  a.win = win;
+  a.w_last = w_last;
+  a.w_prev = w_prev;
+  a.spare = w_last ? g->other(w_last) : nullptr;
+  a.ug = g->ug;
+  a.scr = g->scr;
+  a.area = g->area();
+  a.g = g->g;
+  a.m = g->m;
+  std::memcpy(a.ghost, g->ghost, sizeof a.ghost);
+  a.plan = g->plan;
+  a.mode = mode;
+  a.nsteps = nsteps;
+  return a;
+}
+
 static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, double* log,
                      double dt = 0.0) {
   int rc = FVM_OK;
@@ -686,6 +777,20 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
     double* prev = nsteps % 2 ? g->cur : other;
     const StepArgs a = g->step_args(g->cur, other, kDtAdaptive);
     rc = dev_err(launch_resident_run(a, kernel_model(g->p), last, prev, nsteps, g->stream));
+    if (rc) return rc;
+    g->cur = last;
+    g->speeds_valid = true;
+    return FVM_OK;
+  }
+  if (kind != 2 && nsteps > 0 && cluster_ok(g)) {
+    double* other = g->other(g->cur);
+    double* last = nsteps % 2 ? other : g->cur;
+    cluster::Args a = cluster_args(
+        g, kind == 0 ? kDtAdaptive : (kind == 3 ? kDtFixedCheck : kDtArray), nsteps, g->cur, last,
+        g->other(last));
+    a.dts = dts;
+    a.dt_arg = dt;
+    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
     if (rc) return rc;
     g->cur = last;
     g->speeds_valid = true;
@@ -744,6 +849,16 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
     rc = dev_err(hipMemcpyAsync(ckpts[0], g->cur, bytes, hipMemcpyDeviceToDevice, g->stream));
     if (rc) return rc;
   }
+  if (nsteps > 0 && nck - 1 <= cluster::kMaxSaves && cluster_ok(g)) {
+    double* last = g->other(g->cur);
+    cluster::Args a = cluster_args(g, kDtAdaptive, nsteps, g->cur, last, nullptr);
+    a.every = ckpt_every;
+    a.nsaves = nck - 1;
+    for (int s = 1; s < nck; ++s) a.saves[s - 1] = ckpts[s];
+    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+    if (rc == FVM_OK) g->cur = last;
+    return rc;
+  }
   const double* in = g->cur;
   for (int k = 0; k < nsteps; ++k) {
     double* out;
@@ -771,6 +886,7 @@ int fvm_set_tiling(fvm_grid* g, int rows, int wpb) {
   const int r = rows ? rows : g->rows;
   const int w = wpb ? wpb : g->wpb;
   if (!valid_tiling(r, w)) return FVM_EINVAL;
+  g->strips_asked = rows || wpb;
   if (r != g->rows || w != g->wpb) g->clear_graphs();
   g->rows = r;
   g->wpb = w;
@@ -1049,6 +1165,7 @@ int fvm_autotune(fvm_grid* g, const char* cache_path) {
 
 int fvm_set_cells_per_lane(fvm_grid* g, int cpl) {
   if (!g || cpl < 0 || cpl > 2) return FVM_EINVAL;
+  g->strips_asked = g->strips_asked || cpl != 0;
   g->cpl_req = cpl;
   choose_layout(g);
   return FVM_OK;
@@ -1171,7 +1288,19 @@ int fvm_adjoint_run(fvm_grid* g, double* const* ckpts, int ckpt_every, const dou
     const int k1 = std::min(nsteps, k0 + ckpt_every);
     // recompute W^{k0+1} .. W^{k1-1} into seg_buf[0 .. k1-k0-2]
     const double* in = ckpts[s];
-    for (int k = k0; k + 1 < k1; ++k) {
+    int k = k0;
+    if (k1 - k0 - 1 > 0 && k1 - k0 - 1 <= cluster::kMaxSaves && cluster_ok(g)) {
+      cluster::Args a = cluster_args(g, kDtArray, k1 - k0 - 1, in, nullptr, nullptr);
+      a.dts = dts_dev;
+      a.k0 = k0;
+      a.every = 1;
+      a.nsaves = a.nsteps;
+      for (int q = 0; q < a.nsaves; ++q) a.saves[q] = seg_buf + static_cast<size_t>(q) * state;
+      const int rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+      if (rc) return rc;
+      k = k1;
+    }
+    for (; k + 1 < k1; ++k) {
       double* out = seg_buf + static_cast<size_t>(k - k0) * state;
       StepArgs a = g->step_args(in, out, kDtArray);
       a.dts = dts_dev;
@@ -1254,7 +1383,6 @@ int fvm_run_noalloc(const fvm_params* p, double* w_a, double* w_b, const double*
     return FVM_EINVAL;
   if ((p->model == FVM_SPRAY) != (ug != nullptr)) return FVM_EINVAL;
   if (p->bc == FVM_DIRICHLET || p->closure != FVM_CLOSURE_LOGNORMAL) return FVM_EUNSUPPORTED;
-  if (fvm_scratch_bytes(p) > kNoAllocScratchBytes) return FVM_EINVAL;  // beyond the array
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return FVM_EDEVICE;
   GridScratch* scr = static_cast<GridScratch*>(noalloc_scratch(dev));

@@ -115,13 +115,40 @@ __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsig
   return a > b ? a : b;
 }
 
+// x of the lane the DPP control C names, own x where there is none
+template <int C>
+__device__ __forceinline__ unsigned long long dpp64(unsigned long long x) {
+  const int lo = static_cast<int>(x), hi = static_cast<int>(x >> 32);
+  const int l = __builtin_amdgcn_update_dpp(lo, lo, C, 0xF, 0xF, false);
+  const int h = __builtin_amdgcn_update_dpp(hi, hi, C, 0xF, 0xF, false);
+  return (static_cast<unsigned long long>(static_cast<unsigned int>(h)) << 32) |
+         static_cast<unsigned int>(l);
+}
+
+// Largest x of the wave, in every lane: DPP row shifts by 1, 2, 4 and 8 leave
+// each row's maximum in its last lane, two row broadcasts the wave's in lane
+// 63 (register moves; six rounds through the LDS crossbar take about four
+// times as long, twice a step).
 __device__ __forceinline__ unsigned long long wave_max64(unsigned long long x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  x = umax64(x, dpp64<0x111>(x));
+  x = umax64(x, dpp64<0x112>(x));
+  x = umax64(x, dpp64<0x114>(x));
+  x = umax64(x, dpp64<0x118>(x));
+  x = umax64(x, dpp64<0x142>(x));
+  x = umax64(x, dpp64<0x143>(x));
+  return (static_cast<unsigned long long>(
+              static_cast<unsigned int>(__builtin_amdgcn_readlane(static_cast<int>(x >> 32), 63)))
+          << 32) |
+         static_cast<unsigned int>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
+#else
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const unsigned long long y = __shfl_xor(x, o, 64);
     x = umax64(x, y);
   }
   return x;
+#endif
 }
 
 // ---- the marching wave strip ----------------------------------------------------------

@@ -1,0 +1,144 @@
+"""Runs that keep the whole state in the LDS of all CUs (one launch a run)
+against the same runs as step launches: states, dts, dt log, maxima and status
+bit for bit (both evaluate every face and update with the same arguments, so no
+tolerance), for every model and boundary condition, at the edges of tiles: one
+column or row more than a tile, narrower last tiles, fewer rows than waves,
+several tiles in each direction, the largest grids that fit and the first that
+do not; adaptive, fixed and given dts, checkpointed runs and their backward
+pass, runs in a row, and two grids on two streams."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1701_05431_amd import _lib, inputs
+from paper_1701_05431_amd.solver import Solver, params_from
+
+pytestmark = pytest.mark.gpu
+
+GH = {0: [[0.3], [0.1], [0.2], [0.4]],
+      1: [[1.0, 0.2, -0.1, 2.6], [0.8, -0.1, 0.1, 2.2], [0.9, 0.0, 0.2, 2.4], [1.1, 0.1, 0.0, 2.8]],
+      2: [[1.0, 0.45, 0.21, 0.1, 0.05, -0.02]] * 4}
+
+
+def solvers(model, bc, nx, ny, layout=0, pad=0, **kw):
+    """The grid twice: kept on the chip, and as step launches."""
+    ug = None
+    if model == 2:
+        W, ug = inputs.spray_state(nx, ny, 5)
+    elif model == 1:
+        W = inputs.perturbed_riemann_state(nx, ny, 3)
+    else:
+        W = inputs.advection_state(nx, ny, 2)
+    base = dict(model=model, bc=bc, nx=nx, ny=ny, ld=nx + pad, layout=layout, ax=0.8, ay=-0.6,
+                K=0.05, cfl=0.4)
+    base.update(kw)
+    out = []
+    for resident in (True, False):
+        s = Solver(params_from(**base), ug=ug)
+        s.set_resident_runs(resident)
+        if bc == 2:
+            s.set_boundary_states(GH[model])
+        s.set_state(W)
+        out.append(s)
+    return out, W
+
+
+def same(a, b):
+    torch.cuda.synchronize()
+    assert torch.equal(a.state(), b.state())
+    assert a.cfl_dt() == b.cfl_dt()
+    assert a.sync() == b.sync()
+
+
+SHAPES = [(97, 193), (62, 80), (63, 81), (125, 64), (200, 150), (1, 300), (311, 3), (500, 7)]
+
+
+@pytest.mark.parametrize("model", [0, 1, 2])
+@pytest.mark.parametrize("bc", [0, 1, 2])
+def test_runs_equal_step_launches(model, bc):
+    for n, (nx, ny) in enumerate(SHAPES):
+        print(f"model {model} bc {bc} {nx}x{ny}", flush=True)
+        (a, b), _ = solvers(model, bc, nx, ny, layout=n % 2, pad=n % 3)
+        for steps in (1, 2, 7):
+            da, db = a.run(steps, record_dt=True), b.run(steps, record_dt=True)
+            assert torch.equal(da, db)
+            same(a, b)
+        # the state before the last one is in the other buffer
+        oa, ob = (s.wb if s.current_storage() is s.wa else s.wa for s in (a, b))
+        assert torch.equal(oa, ob)
+        dt = 0.3 * b.cfl_dt()[0]
+        for s in (a, b):
+            s.run_fixed(3, dt)
+            s.run_dts([dt, 0.5 * dt, 0.25 * dt, dt])
+        same(a, b)
+
+
+@pytest.mark.parametrize("model,nx,ny", [(0, 2108, 2400), (1, 1024, 1024), (1, 1054, 1140),
+                                         (1, 1056, 1156), (2, 868, 900), (2, 900, 910)])
+def test_the_largest_grids(model, nx, ny):
+    print(model, nx, ny, flush=True)
+    (a, b), _ = solvers(model, 1 if model == 1 else 0, nx, ny, layout=1)
+    da, db = a.run(5, record_dt=True), b.run(5, record_dt=True)
+    assert torch.equal(da, db)
+    same(a, b)
+
+
+def test_failed_checks_and_bad_states():
+    (a, b), W = solvers(1, 1, 130, 90)
+    for s in (a, b):
+        s.run_fixed(3, 1.0)  # far beyond the CFL bound: the state stays
+        assert s.sync() == _lib.FVM_ECFL
+        assert np.array_equal(s.state().cpu().numpy(), W)
+        assert s.status(clear=True) == _lib.FVM_ECFL
+        s.run(2)
+        assert s.sync() == 0
+    bad = W.copy()
+    bad[0, 40, 70] = -1.0
+    for s in (a, b):
+        s.set_state(bad)
+        s.run(3)
+        assert s.sync() == _lib.FVM_ENONFINITE
+
+
+@pytest.mark.parametrize("model,every", [(1, 1), (1, 4), (2, 3), (0, 5)])
+def test_checkpointed_runs_and_gradients(model, every):
+    (a, b), W = solvers(model, 0 if model == 2 else 1, 150, 110, layout=1)
+    got = []
+    for s in (a, b):
+        s.set_state(W)
+        ck, dts = s.run_ckpt(11, every)
+        end = s.state()
+        lam = s.adjoint(ck, every, dts, torch.ones_like(end))
+        got.append((end, dts, lam.clone(), [c.clone() for c in ck]))
+        assert s.sync() == 0
+        s.run(3)
+    (ea, ta, la, ca), (eb, tb, lb, cb) = got
+    assert torch.equal(ea, eb) and torch.equal(ta, tb) and torch.equal(la, lb)
+    for x, y in zip(ca, cb):
+        assert torch.equal(x, y)
+    same(a, b)
+
+
+def test_two_grids_on_two_streams():
+    (a, ra), _ = solvers(1, 1, 700, 700)
+    (b, rb), _ = solvers(1, 0, 640, 500)
+    torch.cuda.synchronize()
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(4):
+        with torch.cuda.stream(sa):
+            a.run(5)
+        with torch.cuda.stream(sb):
+            b.run(7)
+    torch.cuda.synchronize()
+    ra.run(20)
+    rb.run(28)
+    same(a, ra)
+    same(b, rb)
+
+
+def test_a_chosen_strip_shape_still_runs_strips():
+    (a, b), _ = solvers(1, 1, 200, 150)
+    a.set_tiling(8, 2)
+    a.run(4)
+    b.run(4)
+    same(a, b)
