@@ -248,10 +248,9 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every,
  *               FVM_EINVAL (every speed zero and dt_max == 0).
  * The steps, tile shape and results are those of fvm_run with the default
  * tiling (bitwise: the result does not depend on the tiling). The scratch
- * block (fvm_scratch_bytes(p) bytes, at most 256) lives in a static device
- * array of 256 bytes per device, kept until the process ends; parameters
- * needing more are rejected with FVM_EINVAL. Each call clears it with a
- * kernel before its steps. Calls that overlap on one device (several host
+ * block of the step launches (256 bytes) lives in a static device array of
+ * 256 bytes per device, kept until the process ends. Each call clears it with
+ * a kernel before its steps. Calls that overlap on one device (several host
  * threads, or several streams in flight) share that array and race.
  * Invalid arguments are rejected before anything is enqueued. */
 int fvm_run_noalloc(const fvm_params* p, double* w_a, double* w_b,

@@ -529,8 +529,6 @@ static int enqueue_cfl(fvm_grid* g, double* dt_dev) {
   a.dt_out = dt_dev;
   a.g = g->g;
   a.m = g->m;
-  const long long cells = static_cast<long long>(g->g.nx) * g->g.ny;
-  a.nblocks = static_cast<int>(std::min<long long>(2048, (cells + 255) / 256));
   const int rc = dev_err(launch_cfl(a, g->p.model, g->stream));
   if (rc == FVM_OK) g->speeds_valid = true;
   return rc;
@@ -1404,8 +1402,6 @@ int fvm_run_noalloc(const fvm_params* p, double* w_a, double* w_b, const double*
   c.scr = scr;
   c.g = geom;
   c.m = mc;
-  const long long cells = static_cast<long long>(p->nx) * p->ny;
-  c.nblocks = static_cast<int>(std::min<long long>(2048, (cells + 255) / 256));
   rc = dev_err(launch_cfl(c, p->model, st));
   if (rc == FVM_OK) rc = dev_err(launch_set_log(scr, 1, dts_dev, nsteps, 1, st));
   if (rc) return rc;

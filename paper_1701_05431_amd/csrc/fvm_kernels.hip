@@ -101,21 +101,12 @@ __global__ FVM_STEP_BOUNDS(WPB) void step_kernel(StepArgs a) {
 
 // Speed maxima of a state and the adaptive dt (the checkTimeStep task).
 template <class M>
-__global__ __launch_bounds__(256) void cfl_kernel(CflArgs a) {
+__global__ __launch_bounds__(kCflWaves * kWave) void cfl_kernel(CflArgs a) {
   const M m(a.m);
   unsigned long long bx = 0, by = 0;
-  const long long ncell = static_cast<long long>(a.g.nx) * a.g.ny;
-  for (long long c = blockIdx.x * 256ll + threadIdx.x; c < ncell; c += 256ll * gridDim.x) {
-    const int j = static_cast<int>(c / a.g.nx), i = static_cast<int>(c % a.g.nx);
-    double w[M::NV];
-#pragma unroll
-    for (int v = 0; v < M::NV; ++v) w[v] = a.w[v * a.g.plane + static_cast<size_t>(j) * a.g.ld + i];
-    double sx, sy;
-    m.speeds(w, sx, sy);
-    bx = umax64(bx, bits(sx));
-    by = umax64(by, bits(sy));
-  }
-  if (block_commit<4>(bx, by, a.scr, gridDim.x) && threadIdx.x == 0)
+  row_speeds<kCflWaves>(m, a.w, a.g, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), bx,
+                        by);
+  if (block_commit<kCflWaves>(bx, by, a.scr, gridDim.x) && threadIdx.x == 0)
     finalize_grid(a.scr, a.g, 0.0, false, a.dt_out);
 }
 
@@ -214,7 +205,7 @@ hipError_t launch_cfl(const CflArgs& a, int model, hipStream_t st) {
   else if (model == 1) f = reinterpret_cast<void*>(&cfl_kernel<Euler>);
   else if (model == 2) f = reinterpret_cast<void*>(&cfl_kernel<Spray>);
   if (!f) return hipErrorInvalidValue;
-  return hipLaunchKernel(f, dim3(a.nblocks), dim3(256), args, 0, st);
+  return hipLaunchKernel(f, dim3(cfl_blocks(a.g)), dim3(kCflWaves * kWave), args, 0, st);
 }
 
 hipError_t launch_clear_scratch(GridScratch* s, int n, hipStream_t st) {

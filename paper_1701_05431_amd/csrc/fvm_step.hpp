@@ -540,6 +540,43 @@ __device__ __forceinline__ bool block_commit(unsigned long long bx, unsigned lon
   return last;
 }
 
+// Folds the speeds of a grid's cells into (bx, by), this workgroup's share of
+// `blocks` (workgroups of WPB waves). A wave takes pieces of 64 consecutive
+// cells of a row, four pieces at a time so that their loads are in flight
+// together; the pieces are numbered row by row and dealt round-robin.
+template <int WPB, class M>
+__device__ __forceinline__ void row_speeds(const M& m, const double* __restrict__ w,
+                                           const GridGeom& g, int block, int blocks,
+                                           unsigned long long& bx, unsigned long long& by) {
+  constexpr int NV = M::NV, U = 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int per_row = (g.nx + kWave - 1) / kWave;
+  const long long pieces = static_cast<long long>(per_row) * g.ny;
+  const long long stride = static_cast<long long>(WPB) * blocks;
+  for (long long p = static_cast<long long>(WPB) * block + wave_index(); p < pieces; p += U * stride) {
+    double W[U][NV];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long q = p + u * stride;
+      const long long c = q < pieces ? q : p;
+      const int j = static_cast<int>(c / per_row);
+      const int i = static_cast<int>(c - static_cast<long long>(j) * per_row) * kWave + lane;
+      ok[u] = q < pieces && i < g.nx;
+      const size_t at = static_cast<size_t>(j) * g.ld + min(i, g.nx - 1);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) W[u][v] = w[v * g.plane + at];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double sx, sy;
+      m.speeds(W[u], sx, sy);
+      bx = umax64(bx, ok[u] ? bits(sx) : 0ull);
+      by = umax64(by, ok[u] ? bits(sy) : 0ull);
+    }
+  }
+}
+
 // dt of this launch, and for a fixed-dt step the paper's check
 // dt * max(Sx, Sy) <= min(dx, dy) (a failed check makes the step a copy).
 __device__ __forceinline__ double launch_dt(const StepArgs& a, bool& cfl_fail) {
