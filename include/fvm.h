@@ -425,13 +425,13 @@ int fvm_batch_sync(fvm_batch* b);
  * 0 keeps the current value. Results do not depend on it. */
 int fvm_batch_set_tiling(fvm_batch* b, int rows_per_strip, int waves_per_block);
 
-/* Launch schedule of the batched step: persistent != 0 (the default) runs a
- * resident set of workgroups that take work items from an atomic queue;
- * 0 launches one workgroup per item and lets the hardware dispatcher
- * balance them. fit_blocks != 0 cuts each grid into row blocks (at most the
- * tiling's rows high) whose strip count fills whole workgroups where that
- * costs fewer wave-rows than idle waves would; 0 (the default) keeps blocks
- * of the tiling's height. Results are bitwise the same either way. */
+/* Launch schedule of the batched step: persistent != 0 runs a resident set
+ * of workgroups that take work items from an atomic queue; 0 (the default)
+ * launches one workgroup per item and lets the hardware dispatcher balance
+ * them. fit_blocks != 0 (the default) cuts each grid into row blocks (at most
+ * the tiling's rows high) whose strip count fills whole workgroups where that
+ * costs fewer wave-rows than idle waves would; 0 keeps blocks of the tiling's
+ * height. Results are bitwise the same either way. */
 int fvm_batch_set_schedule(fvm_batch* b, int persistent, int fit_blocks);
 
 /* Lane layout of the batched step: cells_per_lane 2 (the default) runs two

@@ -20,6 +20,7 @@
 #include "fvm_cluster.hpp"
 #include "fvm_host.hpp"
 #include "fvm_internal.hpp"
+#include "fvm_models.hpp"
 
 namespace fvm {
 void* step_kernel_ptr(int model, int bc, int wpb, int cpl, bool halo);
@@ -151,24 +152,76 @@ Tiling adjoint_tiling(const GridGeom& g, int rows, int wpb, int cpl) {
   return t;
 }
 
-// Default tile shape for a grid: the widest workgroup (up to 8 strips) the
-// grid's width fills, and the tallest strips (up to 64 rows) that still give
-// about 2048 wave strips, i.e. two per SIMD on 256 CUs. On the 4096^2 Euler
-// grid this is the measured optimum (64 rows, 8 strips); smaller grids get
-// shorter strips instead of idle CUs. fvm_autotune refines it by measurement.
+// Strip shape for strips_x x ny strip-rows: waves per workgroup (at most wmax)
+// and rows per strip. A launch is over when its last workgroup is, so the
+// workgroups should fill the chip's slots (per_cu waves on each of 256 CUs) a
+// whole number of times: for each width the rows are the fewest that do so in
+// as few rounds as keep them within max_rows, rounded up to the strip's
+// unrolled rows, and the width is the one that leaves the least of the slots'
+// wave-rows idle. Before, strips were sized for about 2048 waves whatever the
+// rounds: Euler 2000^2 84.6 -> 55.6 us a step, 1531 x 997 at an odd pitch
+// 47.7 -> 32.6, 4096^2 189.9 -> 181.0; spray 2048^2 100.0 -> 84.9, 1500 x 1100
+// 60.1 -> 48.1; advection 3000 x 2500 42.6 -> 32.4; the adjoint of 1024^2 36.0 ->
+// 26.0, of 4096^2 384 -> 323.
+void fit_strips(long long strips_x, int ny, int per_cu, int unroll, int max_rows, int wmax,
+                int* rows, int* wpb) {
+  double best = 0.0;
+  for (int w = wmax < per_cu ? wmax : per_cu; w >= 1; w /= 2) {
+    const long long tiles_x = (strips_x + w - 1) / w;
+    long long r = max_rows, rounds = 1;
+    for (; rounds < 4096; ++rounds) {
+      const long long ty = 256 * rounds * (per_cu / w) / tiles_x;
+      if (ty < 1) continue;
+      r = ((ny + ty - 1) / ty + unroll - 1) / unroll * unroll;
+      if (r <= max_rows) break;
+    }
+    r = r > max_rows ? max_rows : r;
+    const double used = static_cast<double>(strips_x) * ny / (rounds * 256.0 * per_cu * r);
+    if (used > 1.03 * best) {
+      best = used;
+      *rows = static_cast<int>(r);
+      *wpb = w;
+    }
+  }
+}
+
+// Lane layout and strip shape of the step for a grid whose buffers allow two
+// cells per lane or not (wide). A grid of few cells takes one cell per lane and
+// three rows (one turn of that strip's unrolled ring): the launch is as long
+// as one strip, and 200 x 150 Euler cells take 8.2 us a step so, 130 x 96 7.5,
+// against 10.3 and 10.2 in two-cells-per-lane strips of four rows (spray 200^2
+// 10.5 against 14.7); from 512^2 on the wide strips are as fast or faster.
+constexpr long long kFewStrips = 700;
+int default_layout(const fvm_params& p, bool wide) {
+  const long long strips = static_cast<long long>((p.nx + kWave - 1) / kWave) * ((p.ny + 2) / 3);
+  return wide && strips > kFewStrips ? 2 : 1;
+}
 void default_tiling(const fvm_params& p, int cpl, int* rows, int* wpb) {
-  // the spray step holds more registers per lane (fewer waves fit), the
-  // advection step far fewer
-  const long long target = p.model == FVM_SPRAY ? 1024 : (p.model == FVM_ADV ? 4096 : 2048);
-  const int wmax = p.model == FVM_SPRAY ? 4 : 8;
-  const int width = strip_width(cpl);
-  const long long strips_x = (p.nx + width - 1) / width;
-  int w = 1;
-  while (w < wmax && 2 * w <= strips_x) w *= 2;
-  long long r = strips_x * p.ny / target;
-  r = r < 4 ? 4 : (r > 64 ? 64 : r);
-  *rows = static_cast<int>(r);
-  *wpb = w;
+  const long long strips_x = (p.nx + strip_width(cpl) - 1) / strip_width(cpl);
+  const bool transport = p.closure == FVM_CLOSURE_MAXENT;
+  // rows of a strip's unrolled loop: loads in flight and two
+  int unroll;
+  if (p.model == FVM_ADV) unroll = 2 + (cpl == 2 ? FVM_PREFETCH2_ADV : FVM_PREFETCH1_ADV);
+  else if (p.model == FVM_EULER) unroll = 2 + (cpl == 2 ? FVM_PREFETCH2_EULER : FVM_PREFETCH1_EULER);
+  else if (transport) unroll = 3;
+  else unroll = 2 + (cpl == 2 ? FVM_PREFETCH2_SPRAY : FVM_PREFETCH1_SPRAY);
+  if (cpl == 1 && default_layout(p, true) == 1) {
+    int w = 1;
+    while (w < 8 && w < strips_x) w *= 2;
+    *rows = unroll;
+    *wpb = w;
+    return;
+  }
+  // waves a CU runs well: one per SIMD for Euler's two-cells-per-lane strips
+  // (256 registers), two for the others
+  const int per_cu = p.model == FVM_EULER && cpl == 2 ? 4 : 8;
+  fit_strips(strips_x, p.ny, per_cu, unroll, 128, 8, rows, wpb);
+}
+
+// The adjoint's strips: 62 columns, two waves per SIMD, four unrolled rows;
+// tiles taller than 16 rows run slower although they re-read fewer rows.
+void default_adjoint_tiling(const fvm_params& p, int* rows, int* wpb) {
+  fit_strips((p.nx + kOutPerWave - 1) / kOutPerWave, p.ny, 8, 4, 16, 4, rows, wpb);
 }
 
 bool valid_tiling(int rows, int wpb) {
@@ -261,6 +314,7 @@ struct fvm_grid {
   bool resident = true;  // grids that fit on the chip keep the state there for a whole run
   cluster::Plan plan{};  // .. their tiles, and whether there are any
   bool plan_ok = false;
+  bool default_strips = true;  // rows and wpb are the default for the layout
   bool strips_asked = false;  // the caller chose a strip shape: its runs are step launches
   int device = -1;
   int cpl = 1;       // layout in use
@@ -349,8 +403,8 @@ int fvm_create(const fvm_params* p, fvm_grid** out) {
   if (!g) return FVM_EINVAL;
   g->p = *p;
   g->nv = fvm_nvar(p->model);
-  default_tiling(*p, 2, &g->rows, &g->wpb);
-  default_tiling(*p, 1, &g->adj_rows, &g->adj_wpb);
+  default_tiling(*p, default_layout(*p, p->ld % 2 == 0), &g->rows, &g->wpb);
+  default_adjoint_tiling(*p, &g->adj_rows, &g->adj_wpb);
   g->g = grid_geometry(*p);
   g->m = model_consts(*p);
   g->plan_ok = cluster_plan(*p, &g->plan);
@@ -380,10 +434,11 @@ static int adjoint_cpl(const fvm_grid* g, const double* w, const double* li, con
 }
 
 static void choose_layout(fvm_grid* g) {
-  const int want = g->cpl_req ? g->cpl_req : 2;
-  const int cpl = (want == 2 && g->bound && wide_layout_ok(g)) ? 2 : 1;
+  const bool wide = g->bound && wide_layout_ok(g);
+  const int cpl = g->cpl_req ? (wide ? g->cpl_req : 1) : default_layout(g->p, wide);
   if (cpl != g->cpl) g->clear_graphs();
   g->cpl = cpl;
+  if (g->default_strips && g->bound) default_tiling(g->p, cpl, &g->rows, &g->wpb);
 }
 
 int fvm_bind(fvm_grid* g, double* w_a, double* w_b, const double* ug, void* scratch,
@@ -884,7 +939,10 @@ int fvm_set_tiling(fvm_grid* g, int rows, int wpb) {
   const int r = rows ? rows : g->rows;
   const int w = wpb ? wpb : g->wpb;
   if (!valid_tiling(r, w)) return FVM_EINVAL;
-  g->strips_asked = rows || wpb;
+  if (rows || wpb) {
+    g->strips_asked = true;
+    g->default_strips = false;
+  }
   if (r != g->rows || w != g->wpb) g->clear_graphs();
   g->rows = r;
   g->wpb = w;
@@ -1107,6 +1165,7 @@ int fvm_autotune(fvm_grid* g, const char* cache_path) {
     g->rows = rows;
     g->wpb = wpb;
     g->cpl_req = cpl;
+    g->default_strips = false;
     g->clear_graphs();
     choose_layout(g);
     return tune_adjoint(g, cache_path, key + " adjoint", g->cur, g->other(g->cur),
@@ -1116,6 +1175,7 @@ int fvm_autotune(fvm_grid* g, const char* cache_path) {
   const int wpbs[4] = {1, 2, 4, 8};
   const int rowss[10] = {4, 8, 16, 32, 48, 64, 96, 128, 192, 256};
   const int save_req = g->cpl_req;
+  g->default_strips = false;
   auto apply = [&](const TuneCand& c) {
     g->cpl_req = c.cpl;
     choose_layout(g);
@@ -1390,7 +1450,8 @@ int fvm_run_noalloc(const fvm_params* p, double* w_a, double* w_b, const double*
   const GridGeom geom = grid_geometry(*p);
   const ModelConsts mc = model_consts(*p);
   auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  const int cpl = p->ld % 2 == 0 && al16(w_a) && al16(w_b) && (!ug || al16(ug)) ? 2 : 1;
+  const int cpl = default_layout(
+      *p, p->ld % 2 == 0 && al16(w_a) && al16(w_b) && (!ug || al16(ug)));
   int rows = kDefaultRows, wpb = kDefaultWpb;
   default_tiling(*p, cpl, &rows, &wpb);
 
