@@ -36,7 +36,7 @@ hipError_t launch_spray_adjoint(const AdjointArgs& a, const double* ug, hipStrea
                                 bool src);
 hipError_t launch_maxent_adjoint_source(const AdjointArgs& a, const double* ug, hipStream_t st);
 namespace cluster {
-hipError_t launch_clear_area(u64* area, size_t words, hipStream_t st);
+hipError_t launch_clear_area(GridScratch* scr, size_t words, hipStream_t st);
 hipError_t launch_run(const Args& a, int model, hipStream_t st);
 }  // namespace cluster
 
@@ -467,9 +467,8 @@ int fvm_bind(fvm_grid* g, double* w_a, double* w_b, const double* ug, void* scra
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess)
       return FVM_EDEVICE;
     if (g->device >= kTurnDevices || cus < g->plan.tiles) g->device = -1;
-    const int rc = dev_err(cluster::launch_clear_area(
-        g->area(), cluster::area_words(g->nv, g->plan), g->stream));
-    if (rc) return rc;
+    return dev_err(
+        cluster::launch_clear_area(g->scr, cluster::area_words(g->nv, g->plan), g->stream));
   }
   return dev_err(launch_clear_scratch(g->scr, 1, g->stream));
 }
@@ -817,6 +816,13 @@ static cluster::Args cluster_args(const fvm_grid* g, int mode, int nsteps, const
   return a;
 }
 
+// One workgroup is the better place for an adaptive run of this grid, or the
+// only one on the chip that is open to it (a captured stream, a strip shape).
+static bool one_workgroup(const fvm_grid* g) {
+  const long long ncell = static_cast<long long>(g->p.nx) * g->p.ny;
+  return resident_ok(g) && (ncell <= resident_cells(fvm_nvar(g->p.model)) || !cluster_ok(g));
+}
+
 static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, double* log,
                      double dt = 0.0) {
   int rc = FVM_OK;
@@ -824,7 +830,7 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
   if ((kind == 0 || kind == 3) && !g->speeds_valid) rc = enqueue_cfl(g, nullptr);
   if (rc == FVM_OK) rc = arm_log(g, log, nsteps);
   if (rc) return rc;
-  if (kind == 0 && nsteps > 0 && resident_ok(g)) {
+  if (kind == 0 && nsteps > 0 && one_workgroup(g)) {
     double* other = g->other(g->cur);
     double* last = nsteps % 2 ? other : g->cur;
     double* prev = nsteps % 2 ? g->cur : other;

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
   }
 
   GridScratch* const s = a.scr;
-  const Divisor dx(g.dx), dy(g.dy);
+  const Spacings h(g);
   double dtn = s->dt;  // adaptive dt of the current state
   double sx = s->cur_sx, sy = s->cur_sy;
   double* const log = s->log;
@@ -187,6 +187,12 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
   const size_t log_stride = static_cast<size_t>(s->log_stride);
   unsigned int status = 0;
   u64 bx = 0, by = 0;
+  int save = 0, next_save = a.every > 0 && a.nsaves > 0 ? a.every : -1;
+  const bool keep = a.w_last || a.w_prev;
+  // transmissive ghost columns: what the first and last columns' lanes write a
+  // second time, this many lanes further
+  const bool mirror_w = BC == kTransmissive && west && lane == 1;
+  const bool mirror_e = BC == kTransmissive && east && lane == ncols;
 
   // k: steps done; publish state k, then make the step from it
   for (int k = 0;; ++k) {
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
       }
       sx = __longlong_as_double(static_cast<long long>(mx));
       sy = __longlong_as_double(static_cast<long long>(my));
-      dtn = next_dt(g, dx, dy, sx, sy);
+      dtn = h.next_dt(g, sx, sy);
       status |= state_status(sx, sy, dtn);
       // every tile is done with state k - 1
       u64* const old = area + ((k - 1) % 3) * set_words + static_cast<size_t>(tile) * words;
@@ -277,18 +283,21 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
         put(maxima + (static_cast<size_t>((k - 1) % 3) * 2 + tid) * P.tiles + tile, kEmpty);
     }
     // where state k goes: a saved state, and the run's last two
-    double* const out[2] = {k > 0 ? saved(a, k) : nullptr,
-                            final ? a.w_last : (k == a.nsteps - 1 ? a.w_prev : nullptr)};
-    for (int q = 0; q < 2; ++q) {
-      double* const w = q == 0 ? out[0] : out[1];
-      if (!w) continue;  // uniform
-      for (int r = jr; r < jr + nr; ++r) {
-        const size_t c = static_cast<size_t>(y0 + r) * g.ld + col;
-        if (inside) {
+    if (k == next_save || (k >= a.nsteps - 1 && keep)) {
+      double* const out[2] = {k == next_save ? a.saves[save] : nullptr,
+                              final ? a.w_last : (k == a.nsteps - 1 ? a.w_prev : nullptr)};
+      for (int q = 0; q < 2; ++q) {
+        double* const w = q == 0 ? out[0] : out[1];
+        if (!w) continue;  // uniform
+        for (int r = jr; r < jr + nr; ++r) {
+          const size_t c = static_cast<size_t>(y0 + r) * g.ld + col;
+          if (inside) {
 #pragma unroll
-          for (int v = 0; v < NV; ++v) w[v * g.plane + c] = S[at(r, v, lane)];
+            for (int v = 0; v < NV; ++v) w[v * g.plane + c] = S[at(r, v, lane)];
+          }
         }
       }
+      if (k == next_save) next_save = ++save < a.nsaves ? next_save + a.every : -1;
     }
     if (final) break;
 
@@ -299,7 +308,8 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
     if (!cfl_ok) status |= kStatusCfl;
     if (tile == 0 && tid == 0 && log && log_n + k < log_cap)
       log[static_cast<size_t>(log_n + k) * log_stride] = dt;
-    const double mux = dx.into(dt), muy = dy.into(dt);
+    double mux, muy;
+    h.courant(dt, mux, muy);
     bx = by = 0;
     if (nr > 0) {  // uniform across the wave
       // the exchanged rows came after the read above
@@ -353,11 +363,14 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
             S[at(r, v, lane)] = Wo[v];
-            if constexpr (BC == kTransmissive) {  // the ghosts that copy this cell
-              if (west && lane == 1) S[at(r, v, 0)] = Wo[v];
-              if (east && lane == ncols) S[at(r, v, ncols + 1)] = Wo[v];
-              if (south && r == 0) S[at(-1, v, lane)] = Wo[v];
-              if (north && r == nrows - 1) S[at(nrows, v, lane)] = Wo[v];
+          }
+          if constexpr (BC == kTransmissive) {
+            if (mirror_w || mirror_e) {
+#pragma unroll
+              for (int v = 0; v < NV; ++v) {
+                if (mirror_w) S[at(r, v, 0)] = Wo[v];
+                if (mirror_e) S[at(r, v, ncols + 1)] = Wo[v];
+              }
             }
           }
         }
@@ -367,6 +380,16 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
           G[v] = Gn[v];
         }
         Pc = Pn;
+      }
+      if constexpr (BC == kTransmissive) {  // the ghost rows copy their neighbours
+        if (south && wave == 0) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) S[at(-1, v, lane)] = S[at(0, v, lane)];
+        }
+        if (north && wave == last_wave) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) S[at(nrows, v, lane)] = S[at(nrows - 1, v, lane)];
+        }
       }
     }
   }
@@ -412,7 +435,7 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
   GridScratch* const s = a.scr;
   const int tid = static_cast<int>(threadIdx.x);
   const long long ncell = static_cast<long long>(g.nx) * g.ny;
-  const Divisor dx(g.dx), dy(g.dy);
+  const Spacings h(g);
   double dtn = s->dt;  // adaptive dt of the current state
   double sx = s->cur_sx, sy = s->cur_sy;
   double* const log = s->log;
@@ -443,7 +466,8 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
     if (!cfl_ok) status |= kStatusCfl;
     if (tid == 0 && log && log_n + k < log_cap)
       log[static_cast<size_t>(log_n + k) * log_stride] = dt;
-    const double mux = dx.into(dt), muy = dy.into(dt);
+    double mux, muy;
+    h.courant(dt, mux, muy);
     u64 bx = 0, by = 0;
     for (long long c = tid; c < ncell; c += kThreads) {
       const int j = static_cast<int>(c / g.nx), i = static_cast<int>(c % g.nx);
@@ -492,7 +516,7 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
     }
     sx = __longlong_as_double(static_cast<long long>(mx));
     sy = __longlong_as_double(static_cast<long long>(my));
-    dtn = next_dt(g, dx, dy, sx, sy);
+    dtn = h.next_dt(g, sx, sy);
     status |= state_status(sx, sy, dtn);
     __syncthreads();
     in = out;
@@ -515,9 +539,11 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
   }
 }
 
-__global__ void clear_area_kernel(u64* area, size_t words) {
+// A grid's scratch block and the exchange area behind it, in one launch.
+__global__ void clear_area_kernel(GridScratch* scr, size_t words) {
   const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < words) area[i] = i < kControlWords ? 0ull : kEmpty;
+  if (i < words) reinterpret_cast<u64*>(scr + 1)[i] = i < kControlWords ? 0ull : kEmpty;
+  if (i == 0) *scr = GridScratch{};
 }
 
 template <class M>
@@ -535,9 +561,9 @@ void* general_fn(int bc) {
 
 }  // namespace
 
-hipError_t launch_clear_area(u64* area, size_t words, hipStream_t st) {
+hipError_t launch_clear_area(GridScratch* scr, size_t words, hipStream_t st) {
   hipLaunchKernelGGL(clear_area_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256),
-                     0, st, area, words);
+                     0, st, scr, words);
   return hipGetLastError();
 }
 

@@ -24,8 +24,8 @@
 // state k + 2 in that set can find state k - 1.
 //
 // Measured, us a step in runs of 20 to 100 steps, step launches / on the chip:
-// advection 512^2 9.6 / 5.9, 1500^2 32.6 / 8.7; Euler 200 x 150 10.4 / 5.9, 512^2
-// 13.9 / 9.5, 1024^2 23.8 / 16.5; spray 200^2 14.8 / 6.0, 512^2 17.3 / 11.7, 860 x 900
+// advection 512^2 9.6 / 5.9, 1500^2 32.6 / 8.7; Euler 200 x 150 10.4 / 5.5, 512^2
+// 13.9 / 9.0, 1024^2 23.8 / 15.3; spray 200^2 14.8 / 6.0, 512^2 17.3 / 11.7, 860 x 900
 // 33.4 / 18.9. About 5 us of each are the exchange (2 us from a store to the
 // neighbour's load), the rest the arithmetic: 1.0 us a row of 8 waves for Euler.
 #pragma once
@@ -80,8 +80,8 @@ __host__ __device__ inline size_t area_words(int nv, const Plan& p) {
 // bytes each, within 160 KB of LDS.
 __host__ __device__ constexpr int max_rows(int nv) { return nv == 1 ? 300 : (nv == 4 ? 76 : 50); }
 // Waves of a workgroup. Two per SIMD for Euler and the spray: with three or
-// four, 1024^2 Euler cells take as long (16.8 and 17.1 us a step against 17.1) and
-// 200 x 150, whose tiles have 8 rows, longer (7.3 and 8.1 us against 5.9).
+// four, 1024^2 Euler cells take as long (16.8 and 17.1 us a step against 17.1 then) and
+// 200 x 150, whose tiles have 8 rows, longer (7.3 and 8.1 us against 5.9 then).
 __host__ __device__ constexpr int waves(int nv) { return nv == 1 ? 16 : 8; }
 
 // The smallest tiles that kMaxTiles workgroups cover the grid with, at least
@@ -122,8 +122,8 @@ struct Args {
 
 // x / d for one d and many x: the quotient from RN(1/d) with two residual
 // corrections, which is the correctly rounded one (the second correction
-// starts within an ulp; P. Markstein, IBM J. Res. Dev. 34, 1990) for the finite
-// normal quotients that occur here; anything else is divided. Five dependent
+// starts within an ulp; P. Markstein, IBM J. Res. Dev. 34, 1990) where x and the
+// quotient are normal and far from the ends of the range. Five dependent
 // operations instead of some thirty, three times in a row between a state's
 // maxima and the step from it.
 struct Divisor {
@@ -131,18 +131,29 @@ struct Divisor {
   __device__ __forceinline__ explicit Divisor(double x) : d(x), r(1.0 / x) {}
   __device__ __forceinline__ double into(double x) const {
     const double q0 = x * r;
-    if (!(fabs(q0) < 1e300 && fabs(q0) > 1e-280)) return x / d;  // uniform: x is
     const double q1 = fma(fma(-d, q0, x), r, q0);
     return fma(fma(-d, q1, x), r, q1);
   }
 };
+__device__ __forceinline__ bool middling(double x) { return x > 1e-100 && x < 1e100; }
 
-// next_dt with the divisors of the grid spacings at hand.
-__device__ __forceinline__ double next_dt(const GridGeom& g, const Divisor& dx, const Divisor& dy,
-                                          double sx, double sy) {
-  if (sx == 0.0 && sy == 0.0) return g.dt_max;
-  return g.cfl / (dx.into(sx) + dy.into(sy));
-}
+// dt / dx and dt / dy, and the next adaptive dt (next_dt) of a state's maxima,
+// with the divisors of the spacings at hand (ordinary: those are middling).
+struct Spacings {
+  Divisor x, y;
+  bool ordinary;
+  __device__ __forceinline__ explicit Spacings(const GridGeom& g)
+      : x(g.dx), y(g.dy), ordinary(middling(g.dx) && middling(g.dy)) {}
+  __device__ __forceinline__ double next_dt(const GridGeom& g, double sx, double sy) const {
+    if (ordinary && middling(sx) && middling(sy)) return g.cfl / (x.into(sx) + y.into(sy));
+    return fvm::next_dt(g, sx, sy);
+  }
+  __device__ __forceinline__ void courant(double dt, double& mux, double& muy) const {
+    const bool fast = ordinary && middling(dt);
+    mux = fast ? x.into(dt) : dt / x.d;
+    muy = fast ? y.into(dt) : dt / y.d;
+  }
+};
 
 // Status bits of a state with these maxima and this next dt, as finalize_grid
 // sets them.

@@ -97,8 +97,14 @@ GridGeom grid_geometry(const fvm_params& p);
 // Cells a wave strip updates: 64 with one cell per lane, 128 with two.
 __host__ __device__ constexpr int strip_width(int cpl) { return cpl == 2 ? 2 * kWave : kWave; }
 
-// LDS doubles of the resident run (two states of nVar x nx x ny): 144 KiB
+// LDS doubles of the resident run in one workgroup (two states of
+// nVar x nx x ny): 144 KiB
 constexpr int kResidentDoubles = 18432;
+// Cells up to which a run in one workgroup beats the same run on several CUs:
+// below, the exchange between CUs costs more than the cells shared out save
+// (us a step, one workgroup / several: advection 64^2 2.7 / 3.8, 80^2 4.2 / 4.1; Euler
+// 32^2 3.9 / 4.7, 40^2 6.0 / 4.6; spray 32^2 4.7 / 5.1, 38^2 6.7 / 5.2).
+__host__ __device__ constexpr int resident_cells(int nv) { return nv == 1 ? 5120 : 1024; }
 
 // Tile decomposition of one grid for a launch.
 struct Tiling {

@@ -13,7 +13,7 @@ namespace fvm {
 
 namespace {
 
-template <class M, int BC>
+template <class M, int BC, bool Wide>
 __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArgs a,
                                                                          double* w_last,
                                                                          double* w_prev,
@@ -21,7 +21,7 @@ __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArg
   constexpr int NV = M::NV;
   constexpr int kThreads = res::threads<M>(), kWaves = kThreads / kWave;
   __shared__ double lds[kResidentDoubles];
-  __shared__ unsigned long long red[2][kWaves];
+  __shared__ unsigned long long red[2][2][kWaves];
   __shared__ double s_dt;
   const M m(a.m);
   const GridGeom& g = a.g;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArg
     for (int v = 0; v < NV; ++v) A[v * ncell + c] = a.win[v * g.plane + at];
   }
   // this thread's cells (tid, tid + 1024, ...) and their neighbours, once
-  constexpr int kCells = res::max_cells<M>();
+  constexpr int kCells = res::max_cells<M, Wide>();
   res::Cell cells[kCells];
   double ugx[kCells], ugy[kCells];
 #pragma unroll
@@ -59,9 +59,10 @@ __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArg
   const unsigned int cap = static_cast<unsigned int>(s->log_cap);
   const size_t stride = static_cast<size_t>(s->log_stride);
   unsigned int st = 0, n = s->nstep;
+  double mux = dt / g.dx, muy = dt / g.dy;
+  unsigned long long last_x = 0, last_y = 0;
   __syncthreads();
   for (int k = 0; k < nsteps; ++k) {
-    const double mux = dt / g.dx, muy = dt / g.dy;
     unsigned long long bx = 0, by = 0;
 #pragma unroll
     for (int q = 0; q < kCells; ++q)
@@ -70,29 +71,52 @@ __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArg
                             by);
     bx = wave_max64(bx);
     by = wave_max64(by);
-    if ((tid & (kWave - 1)) == 0) {
-      red[0][wave] = bx;
-      red[1][wave] = by;
+    const int lane = tid & (kWave - 1), par = k & 1;
+    if (lane == 0) {
+      red[par][0][wave] = bx;
+      red[par][1][wave] = by;
     }
     __syncthreads();
-    if (tid == 0) {
-      unsigned long long mx = red[0][0], my = red[1][0];
+    if (tid == 0 && log) {  // the dt this step used, as the step launches log it
+      if (n < cap) log[static_cast<size_t>(n) * stride] = dt;
+      ++n;
+    }
+    if constexpr (M::NV == 1) {
+      // Constant speeds: the maxima seldom change, so every wave takes them
+      // itself and the step has one barrier (red alternates between two places,
+      // so none is overwritten before all have read it); the dt is computed
+      // again only when they do change. 64^2: 3.80 -> 2.67 us a step.
+      const unsigned long long mx = wave_max64(lane < kWaves ? red[par][0][lane] : 0ull);
+      const unsigned long long my = wave_max64(lane < kWaves ? red[par][1][lane] : 0ull);
+      if (k == 0 || mx != last_x || my != last_y) {  // uniform
+        last_x = mx;
+        last_y = my;
+        sx = __longlong_as_double(static_cast<long long>(mx));
+        sy = __longlong_as_double(static_cast<long long>(my));
+        dt = res::next_step_dt(g, sx, sy, st);
+        mux = dt / g.dx;
+        muy = dt / g.dy;
+      }
+    } else {
+      // The dt changes each step, and its divisions in every wave cost more
+      // than a second barrier (Euler 24^2 3.33 against 3.16 us a step, 32^2 4.28
+      // against 4.12).
+      if (tid == 0) {
+        unsigned long long mx = red[par][0][0], my = red[par][1][0];
 #pragma unroll
-      for (int q = 1; q < kWaves; ++q) {
-        mx = umax64(mx, red[0][q]);
-        my = umax64(my, red[1][q]);
+        for (int q = 1; q < kWaves; ++q) {
+          mx = umax64(mx, red[par][0][q]);
+          my = umax64(my, red[par][1][q]);
+        }
+        sx = __longlong_as_double(static_cast<long long>(mx));
+        sy = __longlong_as_double(static_cast<long long>(my));
+        s_dt = res::next_step_dt(g, sx, sy, st);
       }
-      sx = __longlong_as_double(static_cast<long long>(mx));
-      sy = __longlong_as_double(static_cast<long long>(my));
-      const double dtn = res::next_step_dt(g, sx, sy, st);
-      if (log) {  // the dt this step used, as the step launches log it
-        if (n < cap) log[static_cast<size_t>(n) * stride] = dt;
-        ++n;
-      }
-      s_dt = dtn;
+      __syncthreads();
+      dt = s_dt;
+      mux = dt / g.dx;
+      muy = dt / g.dy;
     }
-    __syncthreads();
-    dt = s_dt;
     double* t = A;
     A = B;
     B = t;
@@ -115,12 +139,18 @@ __global__ __launch_bounds__(res::threads<M>()) void resident_run_kernel(StepArg
   }
 }
 
-template <class M>
+template <class M, bool Wide>
 void* resident_fn(int bc) {
-  if (bc == kPeriodic) return reinterpret_cast<void*>(&resident_run_kernel<M, kPeriodic>);
-  if (bc == kTransmissive) return reinterpret_cast<void*>(&resident_run_kernel<M, kTransmissive>);
-  if (bc == kDirichlet) return reinterpret_cast<void*>(&resident_run_kernel<M, kDirichlet>);
+  if (bc == kPeriodic) return reinterpret_cast<void*>(&resident_run_kernel<M, kPeriodic, Wide>);
+  if (bc == kTransmissive)
+    return reinterpret_cast<void*>(&resident_run_kernel<M, kTransmissive, Wide>);
+  if (bc == kDirichlet) return reinterpret_cast<void*>(&resident_run_kernel<M, kDirichlet, Wide>);
   return nullptr;
+}
+
+template <class M>
+void* resident_fn(int bc, long long ncell) {
+  return ncell <= resident_cells(M::NV) ? resident_fn<M, false>(bc) : resident_fn<M, true>(bc);
 }
 
 }  // namespace
@@ -131,12 +161,12 @@ void* resident_fn(int bc) {
 hipError_t launch_resident_run(const StepArgs& a, int model, double* w_last, double* w_prev,
                                int nsteps, hipStream_t st) {
   void* f = nullptr;
-  if (model == 0) f = resident_fn<Adv>(a.g.bc);
-  else if (model == 1) f = resident_fn<Euler>(a.g.bc);
-  else if (model == 2) f = resident_fn<Spray>(a.g.bc);
+  const long long ncell = static_cast<long long>(a.g.nx) * a.g.ny;
+  if (model == 0) f = resident_fn<Adv>(a.g.bc, ncell);
+  else if (model == 1) f = resident_fn<Euler>(a.g.bc, ncell);
+  else if (model == 2) f = resident_fn<Spray>(a.g.bc, ncell);
   const int nv = model == 0 ? 1 : (model == 1 ? 4 : 6);
-  if (!f || nsteps < 0 ||
-      2LL * nv * a.g.nx * a.g.ny > static_cast<long long>(kResidentDoubles))
+  if (!f || nsteps < 0 || 2 * nv * ncell > kResidentDoubles)
     return hipErrorInvalidValue;
   StepArgs copy = a;
   void* args[] = {&copy, &w_last, &w_prev, &nsteps};

@@ -119,10 +119,12 @@ __device__ __forceinline__ void update_cell(const M& m, const double* gh, const 
   by = umax64(by, bits(sy));
 }
 
-// Cells per thread of a resident run of model M (two states in the LDS).
-template <class M>
+// Cells per thread of a resident run of model M: of the grids that are best in
+// one workgroup, or (Wide) of all that fit (two states in the LDS).
+template <class M, bool Wide>
 constexpr int max_cells() {
-  return (kResidentDoubles / (2 * M::NV) + threads<M>() - 1) / threads<M>();
+  return ((Wide ? kResidentDoubles / (2 * M::NV) : resident_cells(M::NV)) + threads<M>() - 1) /
+         threads<M>();
 }
 
 // The run's bookkeeping after a step with maxima (sx, sy) and dt `used`:

@@ -73,6 +73,24 @@ def test_runs_equal_step_launches(model, bc):
         same(a, b)
 
 
+@pytest.mark.parametrize("model,nx,ny", [(0, 64, 80), (0, 72, 72), (0, 96, 96), (1, 32, 32),
+                                         (1, 33, 32), (1, 48, 48), (2, 1, 1024), (2, 41, 25),
+                                         (2, 39, 39)])
+@pytest.mark.parametrize("strips", [False, True])
+def test_the_limits_of_one_workgroup(model, nx, ny, strips):
+    """The last grids of one workgroup and the first of several; with a strip
+    shape asked for, all of them stay in one workgroup."""
+    print(model, nx, ny, strips, flush=True)
+    for bc in (0, 1, 2):
+        (a, b), _ = solvers(model, bc, nx, ny, pad=bc)
+        if strips:
+            a.set_tiling(8, 4)
+        for steps in (1, 8):
+            da, db = a.run(steps, record_dt=True), b.run(steps, record_dt=True)
+            assert torch.equal(da, db)
+            same(a, b)
+
+
 @pytest.mark.parametrize("model,nx,ny", [(0, 2108, 2400), (1, 1024, 1024), (1, 1054, 1140),
                                          (1, 1056, 1156), (2, 868, 900), (2, 900, 910)])
 def test_the_largest_grids(model, nx, ny):
