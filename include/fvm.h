@@ -183,6 +183,16 @@ int fvm_current(const fvm_grid* g, double** w);
  * unknown. */
 int fvm_set_state(fvm_grid* g, const double* src, int src_on_device);
 
+/* Copies a field in device memory, row j of variable v at
+ * src + v * var_stride + j * row_stride (in doubles) and cols (nx or ld)
+ * doubles long, into dst (nVar * ny * ld doubles) in the grid's ld and layout;
+ * columns beyond cols become zero. dst NULL: into the current buffer, as
+ * fvm_set_state. Asynchronous. FVM_EUNSUPPORTED, and nothing copied, if the two
+ * overlap, if one is not aligned to 8 bytes, if the stream is another device's
+ * than the current one or if the field has more than 2^31 row pieces of 64. */
+int fvm_load(fvm_grid* g, const double* src, long long var_stride, long long row_stride,
+             int cols, double* dst);
+
 /* Copies the current state (ld and layout kept) to dst; a host destination
  * makes the call wait. */
 int fvm_get_state(fvm_grid* g, double* dst, int dst_on_device);
@@ -403,6 +413,13 @@ int fvm_batch_bind(fvm_batch* b, double* w_a, double* w_b, void* scratch,
 
 /* Computes every grid's speed maxima and adaptive dt (asynchronous). */
 int fvm_batch_cfl(fvm_batch* b);
+
+/* Copies src[k], a dense (nVar, ny, nx) field in device memory, into grid k of
+ * the current buffer, for every grid, with its speed maxima and adaptive dt as
+ * fvm_batch_cfl computes them (asynchronous; src itself is read before the call
+ * returns). FVM_EUNSUPPORTED, and nothing done, if stream is not the batch's or a
+ * field overlaps the current buffer or is not aligned to 8 bytes. */
+int fvm_batch_load(fvm_batch* b, const double* const* src, void* stream);
 
 /* nsteps adaptive steps of every grid, one persistent launch per step
  * replayed from a cached HIP graph. dts_dev (nullable) receives

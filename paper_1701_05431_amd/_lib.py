@@ -53,6 +53,7 @@ SIGNATURES = {
     "fvm_set_stream": (C.c_int, [_V, _V]),
     "fvm_current": (C.c_int, [_V, C.POINTER(_V)]),
     "fvm_set_state": (C.c_int, [_V, _V, C.c_int]),
+    "fvm_load": (C.c_int, [_V, _V, C.c_longlong, C.c_longlong, C.c_int, _V]),
     "fvm_get_state": (C.c_int, [_V, _V, C.c_int]),
     "fvm_cfl_dt": (C.c_int, [_V, _V]),
     "fvm_cfl_dt_host": (C.c_int, [_V, _D, _D, _D]),
@@ -82,6 +83,7 @@ SIGNATURES = {
     "fvm_batch_scratch_bytes": (C.c_size_t, [_V]),
     "fvm_batch_bind": (C.c_int, [_V, _V, _V, _V, _V]),
     "fvm_batch_cfl": (C.c_int, [_V]),
+    "fvm_batch_load": (C.c_int, [_V, C.POINTER(_V), _V]),
     "fvm_batch_run": (C.c_int, [_V, C.c_int, _V]),
     "fvm_batch_run_per_grid": (C.c_int, [_V, C.c_int, _V]),
     "fvm_batch_current": (C.c_int, [_V, C.POINTER(_V)]),

@@ -29,6 +29,7 @@ hipError_t launch_resident_run(const StepArgs& a, int model, double* w_last, dou
 hipError_t launch_step(const StepArgs& a, int model, hipStream_t st);
 hipError_t launch_cfl(const CflArgs& a, int model, hipStream_t st);
 hipError_t launch_clear_scratch(GridScratch* s, int n, hipStream_t st);
+hipError_t launch_load(const LoadArgs& a, hipStream_t st);
 hipError_t launch_set_log(GridScratch* s, int n, double* base, int cap, int stride,
                           hipStream_t st);
 hipError_t launch_adjoint(const AdjointArgs& a, int model, const double* ug, hipStream_t st);
@@ -540,6 +541,36 @@ int fvm_set_state(fvm_grid* g, const double* src, int src_on_device) {
   if (e == hipSuccess && !src_on_device) e = hipStreamSynchronize(g->stream);
   g->speeds_valid = false;
   g->me_valid = false;
+  return dev_err(e);
+}
+
+int fvm_load(fvm_grid* g, const double* src, long long var_stride, long long row_stride, int cols,
+             double* dst) {
+  if (!g || !src || !g->bound || var_stride < 0 || row_stride < 0) return FVM_EINVAL;
+  if (cols != g->p.nx && cols != g->p.ld) return FVM_EINVAL;
+  double* const to = dst ? dst : g->cur;
+  const uintptr_t s = reinterpret_cast<uintptr_t>(src), d = reinterpret_cast<uintptr_t>(to);
+  if (s % 8 || d % 8) return FVM_EUNSUPPORTED;
+  const size_t extent = static_cast<size_t>(var_stride) * (g->nv - 1) +
+                        static_cast<size_t>(row_stride) * (g->p.ny - 1) + cols;
+  if (s < d + 8 * g->elems() && d < s + 8 * extent) return FVM_EUNSUPPORTED;
+  int dev = 0, sdev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(g->stream, &sdev) != hipSuccess)
+    return FVM_EDEVICE;
+  if (dev != sdev) return FVM_EUNSUPPORTED;
+  LoadArgs a{};
+  a.src = src;
+  a.dst = to;
+  a.var_stride = var_stride;
+  a.row_stride = row_stride;
+  a.nv = static_cast<unsigned int>(g->nv);
+  a.ny = static_cast<unsigned int>(g->p.ny);
+  a.cols = static_cast<unsigned int>(cols);
+  a.ld = static_cast<unsigned int>(g->p.ld);
+  a.by_rows = g->p.layout == FVM_LAYOUT_ROWS;
+  const hipError_t e = launch_load(a, g->stream);
+  if (e == hipErrorInvalidValue) return FVM_EUNSUPPORTED;  // too many rows for one launch
+  if (!dst) g->speeds_valid = g->me_valid = false;
   return dev_err(e);
 }
 

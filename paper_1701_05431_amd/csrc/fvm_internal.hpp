@@ -168,6 +168,16 @@ struct AdjointArgs {
 
 // ---- batches ---------------------------------------------------------------
 
+// A field on its way into a grid's storage: row j of variable v at
+// src + v * var_stride + j * row_stride, `cols` doubles long.
+struct LoadArgs {
+  const double* src;
+  double* dst;
+  long long var_stride, row_stride;
+  unsigned int nv, ny, cols, ld;
+  bool by_rows;  // dst row j * nv + v, else v * ny + j
+};
+
 struct BatchGrid {            // per-grid record in device memory
   size_t offset;              // element offset of the grid inside the packed buffers
   GridGeom g;

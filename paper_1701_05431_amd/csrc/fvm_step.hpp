@@ -541,13 +541,15 @@ __device__ __forceinline__ bool block_commit(unsigned long long bx, unsigned lon
 }
 
 // Folds the speeds of a grid's cells into (bx, by), this workgroup's share of
-// `blocks` (workgroups of WPB waves). A wave takes pieces of 64 consecutive
+// `blocks` (workgroups of WPB waves); w: variable planes `plane` apart, rows
+// `ld`. COPY: the cells go to `out` (the grid's own plane and ld) on the way. A wave takes pieces of 64 consecutive
 // cells of a row, four pieces at a time so that their loads are in flight
 // together; the pieces are numbered row by row and dealt round-robin.
-template <int WPB, class M>
-__device__ __forceinline__ void row_speeds(const M& m, const double* __restrict__ w,
-                                           const GridGeom& g, int block, int blocks,
-                                           unsigned long long& bx, unsigned long long& by) {
+template <int WPB, bool COPY, class M>
+__device__ __forceinline__ void row_speeds(const M& m, const double* __restrict__ w, size_t plane,
+                                           size_t ld, double* __restrict__ out, const GridGeom& g,
+                                           int block, int blocks, unsigned long long& bx,
+                                           unsigned long long& by) {
   constexpr int NV = M::NV, U = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int per_row = (g.nx + kWave - 1) / kWave;
@@ -556,6 +558,7 @@ __device__ __forceinline__ void row_speeds(const M& m, const double* __restrict_
   for (long long p = static_cast<long long>(WPB) * block + wave_index(); p < pieces; p += U * stride) {
     double W[U][NV];
     bool ok[U];
+    size_t to[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const long long q = p + u * stride;
@@ -563,12 +566,19 @@ __device__ __forceinline__ void row_speeds(const M& m, const double* __restrict_
       const int j = static_cast<int>(c / per_row);
       const int i = static_cast<int>(c - static_cast<long long>(j) * per_row) * kWave + lane;
       ok[u] = q < pieces && i < g.nx;
-      const size_t at = static_cast<size_t>(j) * g.ld + min(i, g.nx - 1);
+      const size_t at = static_cast<size_t>(j) * ld + min(i, g.nx - 1);
+      if constexpr (COPY) to[u] = static_cast<size_t>(j) * g.ld + i;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) W[u][v] = w[v * g.plane + at];
+      for (int v = 0; v < NV; ++v) W[u][v] = w[v * plane + at];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if constexpr (COPY) {
+        if (ok[u]) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) out[v * g.plane + to[u]] = W[u][v];
+        }
+      }
       double sx, sy;
       m.speeds(W[u], sx, sy);
       bx = umax64(bx, ok[u] ? bits(sx) : 0ull);

@@ -65,6 +65,12 @@ def logical(p: _lib.Params, t: torch.Tensor) -> torch.Tensor:
     return t.permute(1, 0, 2) if p.layout == _lib.FVM_LAYOUT_ROWS else t
 
 
+def _readable(W, device) -> bool:
+    """A kernel on `device` can read the tensor's values where they are."""
+    return (type(W) is torch.Tensor and W.dtype == torch.float64 and W.device == device
+            and W.layout == torch.strided and not W.is_neg())
+
+
 class Solver:
     """One grid: two ping-pong state buffers (float64, nVar * Ny * ld each,
     in the layout of p.layout), the spray gas velocity if any, and the
@@ -121,6 +127,29 @@ class Solver:
         logical(p, out)[:, :, :W.shape[2]].copy_(W)
         return out
 
+    def _load(self, W, out=None) -> bool:
+        """Copies W, as _as_state takes it, into the storage tensor `out` (the
+        current state if None) in one pass; False, and nothing done, where the
+        general way is needed."""
+        p = self.p
+        if not _readable(W, self.wa.device) or W.dim() != 3:
+            return False
+        nv, ny, cols = W.shape
+        if nv != self.nv or ny != p.ny or cols not in (p.nx, p.ld):
+            return False
+        sv, sy, sx = W.stride()
+        if sx != 1 and cols > 1:
+            return False
+        try:
+            src = W.data_ptr()
+        except RuntimeError:  # a tensor without storage of its own
+            return False
+        code = lib().fvm_load(self.h, src, sv, sy, cols, _ptr(out))
+        if code == _lib.FVM_EUNSUPPORTED:
+            return False
+        check(code, "fvm_load")
+        return True
+
     def set_boundary_states(self, ghost) -> None:
         """Dirichlet ghost states, shape (4, nVar): west, east, south, north."""
         g = np.ascontiguousarray(np.asarray(ghost, dtype=np.float64).reshape(4, self.nv))
@@ -141,10 +170,13 @@ class Solver:
         lib().fvm_set_stream(self.h, _stream_handle(self.device))
 
     def set_state(self, W) -> None:
-        src = self._as_state(W)
         self._bind_stream()
+        if self._load(W):
+            self._keep = W  # keep the source alive until the copy has run
+            return
+        src = self._as_state(W)
         check(lib().fvm_set_state(self.h, _ptr(src), 1), "fvm_set_state")
-        self._keep = src  # keep the source alive until the copy has run
+        self._keep = src
 
     def current_storage(self) -> torch.Tensor:
         """The buffer holding the current state, in the grid's layout."""
@@ -207,12 +239,13 @@ class Solver:
     def adjoint(self, ckpts, every: int, dts: torch.Tensor, lam: torch.Tensor) -> torch.Tensor:
         """dL/dW^0 from dL/dW^N (lam, shape (nVar, Ny, Nx or ld)) through
         len(dts) steps with the given checkpoints; an (nVar, Ny, ld) view."""
-        lam = self._as_state(lam).clone()
+        self._bind_stream()
+        out = torch.empty(storage_shape(self.p, self.nv), dtype=torch.float64, device=self.device)
+        lam = out if self._load(lam, out) else self._as_state(lam).clone()
         tmp = torch.empty_like(lam)
         seg = torch.empty((max(every - 1, 1),) + tuple(lam.shape), dtype=torch.float64,
                           device=self.device)
         arr = (C.c_void_p * max(len(ckpts), 1))(*[t.data_ptr() for t in ckpts])
-        self._bind_stream()
         check(lib().fvm_adjoint_run(self.h, arr, int(every), _ptr(dts), int(dts.numel()),
                                     _ptr(lam), _ptr(tmp), _ptr(seg)), "fvm_adjoint_run")
         self._keep = (tmp, seg)
@@ -340,7 +373,31 @@ class Batch:
         n = self.nv * p.ny * p.ld
         return logical(p, buf[self.offsets[k]:self.offsets[k] + n].view(storage_shape(p, self.nv)))
 
+    def _load(self, states) -> bool:
+        """Copies all grids' states, and takes their maxima, in one pass; False,
+        and nothing done, where the general way is needed."""
+        if len(states) != self.n:
+            return False
+        dev, grad = self.wa.device, torch.is_grad_enabled()
+        if torch.cuda.current_device() != dev.index:
+            return False
+        for p, W in zip(self.plist, states):
+            if (not _readable(W, dev) or tuple(W.shape) != (self.nv, p.ny, p.nx)
+                    or not W.is_contiguous() or (grad and W.requires_grad)):
+                return False
+        try:
+            src = (C.c_void_p * self.n)(*[W.data_ptr() for W in states])
+        except RuntimeError:  # a tensor without storage of its own
+            return False
+        code = lib().fvm_batch_load(self.h, src, _stream_handle(self.device))
+        if code == _lib.FVM_EUNSUPPORTED:
+            return False
+        check(code, "fvm_batch_load")
+        return True
+
     def set_states(self, states) -> None:
+        if isinstance(states, (list, tuple)) and self._load(states):
+            return
         cur = self.current()
         for k, W in enumerate(states):
             p = self.plist[k]
