@@ -115,12 +115,12 @@ __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsig
   return a > b ? a : b;
 }
 
-// x of the lane the DPP control C names, own x where there is none
+// x of the lane the DPP control C names, 0 where there is none
 template <int C>
 __device__ __forceinline__ unsigned long long dpp64(unsigned long long x) {
   const int lo = static_cast<int>(x), hi = static_cast<int>(x >> 32);
-  const int l = __builtin_amdgcn_update_dpp(lo, lo, C, 0xF, 0xF, false);
-  const int h = __builtin_amdgcn_update_dpp(hi, hi, C, 0xF, 0xF, false);
+  const int l = __builtin_amdgcn_mov_dpp(lo, C, 0xF, 0xF, true);
+  const int h = __builtin_amdgcn_mov_dpp(hi, C, 0xF, 0xF, true);
   return (static_cast<unsigned long long>(static_cast<unsigned int>(h)) << 32) |
          static_cast<unsigned int>(l);
 }
