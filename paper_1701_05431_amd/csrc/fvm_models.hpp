@@ -48,14 +48,14 @@ namespace fvm {
 
 // ---- cross-lane moves ------------------------------------------------------
 // Lane l receives lane l+1's value (wave_shl:1 DPP), resp. lane l-1's value
-// (wave_shr:1). The edge lanes receive 0 from the hardware's bound control (a 0
-// given as the old value is a move before every DPP move); the kernels never use
-// those lanes' results.
+// (wave_shr:1). The edge lanes receive 0 from the hardware's bound control
+// (the last argument; without it the old value 0 is a move before every DPP
+// move); the kernels never use those lanes' results.
 __device__ __forceinline__ int dpp_from_next_i32(int x) {
-  return __builtin_amdgcn_mov_dpp(x, 0x130, 0xF, 0xF, true);
+  return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xF, 0xF, true);
 }
 __device__ __forceinline__ int dpp_from_prev_i32(int x) {
-  return __builtin_amdgcn_mov_dpp(x, 0x138, 0xF, 0xF, true);
+  return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xF, 0xF, true);
 }
 __device__ __forceinline__ double from_next(double x) {
 #if FVM_SHUFFLE_WITH_BPERMUTE

@@ -119,8 +119,8 @@ __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsig
 template <int C>
 __device__ __forceinline__ unsigned long long dpp64(unsigned long long x) {
   const int lo = static_cast<int>(x), hi = static_cast<int>(x >> 32);
-  const int l = __builtin_amdgcn_mov_dpp(lo, C, 0xF, 0xF, true);
-  const int h = __builtin_amdgcn_mov_dpp(hi, C, 0xF, 0xF, true);
+  const int l = __builtin_amdgcn_update_dpp(0, lo, C, 0xF, 0xF, true);
+  const int h = __builtin_amdgcn_update_dpp(0, hi, C, 0xF, 0xF, true);
   return (static_cast<unsigned long long>(static_cast<unsigned int>(h)) << 32) |
          static_cast<unsigned int>(l);
 }
