@@ -35,10 +35,17 @@ __global__ __launch_bounds__(WPB * kWave) void adjoint_kernel(AdjointArgs a) {
     if (xs >= a.g.nx) return;
     // tiles of odd rows march down (vertical neighbours meet at their
     // shared rows)
-    if (ty & 1)
-      adjoint_strip1<M, BC, true>(m, a, xs, j0, j1, mux, muy);
-    else
-      adjoint_strip1<M, BC, false>(m, a, xs, j0, j1, mux, muy);
+    const bool edge = xs == 0 || xs + kOutPerWave >= a.g.nx || j0 == 0 || j1 == a.g.ny;
+    if (edge) {
+      if (ty & 1)
+        adjoint_strip1<M, BC, true, true>(m, a, xs, j0, j1, mux, muy);
+      else
+        adjoint_strip1<M, BC, false, true>(m, a, xs, j0, j1, mux, muy);
+    } else if (ty & 1) {
+      adjoint_strip1<M, BC, true, false>(m, a, xs, j0, j1, mux, muy);
+    } else {
+      adjoint_strip1<M, BC, false, false>(m, a, xs, j0, j1, mux, muy);
+    }
   }
 }
 

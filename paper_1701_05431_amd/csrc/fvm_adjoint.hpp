@@ -32,10 +32,12 @@
 #include "fvm_internal.hpp"
 #include "fvm_models.hpp"
 
-// Rows of (W, lambda) loads in flight per adjoint strip, one and two cells
-// per lane.
+// Rows of (W, lambda) loads in flight per adjoint strip beyond the next row, one
+// cell per lane (Euler; advection: kRowsAhead) and two. None for Euler: the
+// second wave of the SIMD covers the loads as well, and a tile is computed in
+// turns of two rows instead of four (1024^2 22.9 -> 20.3 us, 300^2 7.1 -> 5.8).
 #ifndef FVM_ADJ_PREFETCH
-#define FVM_ADJ_PREFETCH 2
+#define FVM_ADJ_PREFETCH 0
 #endif
 #ifndef FVM_ADJ_PREFETCH2
 #define FVM_ADJ_PREFETCH2 1
@@ -46,6 +48,7 @@ namespace fvm {
 struct AdjAdv {
   static constexpr int NV = 1;
   static constexpr bool kCellA = false;  // face() returns the whole shares
+  static constexpr int kRowsAhead = 2;   // (none: 1024^2 6.1 -> 7.8 us)
   struct Prim {};
   double ax, ay;
   __device__ explicit AdjAdv(const ModelConsts& m) : ax(m.ax), ay(m.ay) {}
@@ -61,6 +64,19 @@ struct AdjAdv {
                                              Prim&) const {
     wr[0] = from_next(w[0]);
   }
+  // (the face does not depend on the cells)
+  struct Side {};
+  template <int D>
+  __device__ __forceinline__ void side(const Prim&, Side&) const {}
+  template <int D>
+  __device__ __forceinline__ void face(const double* wl, const Side&, const double* wr,
+                                       const Side&, const double* d, double* a, double* b) const {
+    face<D>(wl, Prim{}, wr, Prim{}, d, a, b);
+  }
+  __device__ __forceinline__ void shift_next(const double* w, const Side&, double* wr,
+                                             Side&) const {
+    wr[0] = from_next(w[0]);
+  }
 };
 
 struct AdjEuler {
@@ -68,7 +84,10 @@ struct AdjEuler {
   // face() leaves out the 0.5 A(W)^T d terms; each cell adds 0.5 A(W)^T of
   // the sum of its faces' d (at_d), once per axis
   static constexpr bool kCellA = true;
-  struct Prim { double r, u, v, p, c; };
+  static constexpr int kRowsAhead = FVM_ADJ_PREFETCH;
+  struct Prim { double r, u, v, p, c, k; };  // k = gamma / (2 rho c)
+  // What a face needs of a cell along its axis: s = |u_n| + c and ds/dW
+  struct Side { double s, g[4]; };
   double gamma, gm1;
   __device__ explicit AdjEuler(const ModelConsts& m) : gamma(m.gamma), gm1(m.gm1) {}
   // (the forward step's refined reciprocal and square root)
@@ -78,6 +97,7 @@ struct AdjEuler {
     q.v = w[2] * q.r;
     q.p = gm1 * fma(-0.5, fma(w[1], q.u, w[2] * q.v), w[3]);
     q.c = root(gamma * q.p * q.r);
+    q.k = 0.5 * gamma * q.r * recip(q.c);
   }
   // out = A(W)^T d along axis D (written with fused multiply-adds: the
   // kernel is bound by this arithmetic)
@@ -100,10 +120,9 @@ struct AdjEuler {
   __device__ __forceinline__ void dspeed(const Prim& q, double* gs) const {
     const double un = D == 0 ? q.u : q.v;
     const double sr = un >= 0.0 ? q.r : -q.r;  // sign(u_n) / rho
-    const double k = 0.5 * gamma * q.r * recip(q.c);
     const double hq2 = 0.5 * fma(q.u, q.u, q.v * q.v);
-    const double kg = k * gm1;
-    gs[0] = fma(k, fma(gm1, hq2, -q.p * q.r), -sr * un);
+    const double kg = q.k * gm1;
+    gs[0] = fma(q.k, fma(gm1, hq2, -q.p * q.r), -sr * un);
     gs[1] = -kg * q.u;
     gs[2] = -kg * q.v;
     gs[3] = kg;
@@ -131,9 +150,32 @@ struct AdjEuler {
     q.u = left ? pl.u : pr.u;
     q.v = left ? pl.v : pr.v;
     q.p = left ? pl.p : pr.p;
-    q.c = left ? pl.c : pr.c;
+    q.k = left ? pl.k : pr.k;
     double gs[4];
     dspeed<D>(q, gs);
+    shares(wl, wr, left, hs, gs, d, a, b);
+  }
+  // The same from the cells' sides: each cell's ds/dW is formed once for its
+  // two faces along an axis, not once a face.
+  template <int D>
+  __device__ __forceinline__ void side(const Prim& q, Side& o) const {
+    o.s = fabs(D == 0 ? q.u : q.v) + q.c;
+    dspeed<D>(q, o.g);
+  }
+  template <int D>
+  __device__ __forceinline__ void face(const double* wl, const Side& l, const double* wr,
+                                       const Side& r, const double* d, double* a,
+                                       double* b) const {
+    const bool left = l.s >= r.s;
+    const double hs = 0.5 * (left ? l.s : r.s);
+    double gs[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) gs[k] = left ? l.g[k] : r.g[k];
+    shares(wl, wr, left, hs, gs, d, a, b);
+  }
+  __device__ __forceinline__ void shares(const double* wl, const double* wr, bool left, double hs,
+                                         const double* gs, const double* d, double* a,
+                                         double* b) const {
     const double dwd = fma(wr[0] - wl[0], d[0],
                            fma(wr[1] - wl[1], d[1],
                                fma(wr[2] - wl[2], d[2], (wr[3] - wl[3]) * d[3])));
@@ -155,6 +197,16 @@ struct AdjEuler {
     qr.v = from_next(q.v);
     qr.p = from_next(q.p);
     qr.c = from_next(q.c);
+    qr.k = from_next(q.k);
+  }
+  __device__ __forceinline__ void shift_next(const double* w, const Side& q, double* wr,
+                                             Side& qr) const {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      wr[v] = from_next(w[v]);
+      qr.g[v] = from_next(q.g[v]);
+    }
+    qr.s = from_next(q.s);
   }
 };
 
@@ -178,20 +230,21 @@ __device__ __forceinline__ int adj_row(int r, int ny) {
 // holds the prescribed state of its side (gh: ghost[side * kMaxVar + v];
 // `col_side` is the side of a ghost column); with transmissive ones it is the
 // boundary cell, loaded from the clamped index.
-template <int NV, int BC>
+template <int NV, int BC, bool EDGE = true>
 __device__ __forceinline__ void load_adj_row(double* w, double* l, const double* __restrict__ wb,
                                              const double* __restrict__ lb, const GridGeom& g,
-                                             int r, bool ghost_col, const double* gh = nullptr,
-                                             int col_side = 0) {
-  const size_t off = static_cast<size_t>(adj_row<BC>(r, g.ny)) * g.ld;
-  const bool ghost_row = BC != 0 && (r < 0 || r >= g.ny);
+                                             int r, unsigned int col, bool ghost_col,
+                                             const double* gh = nullptr, int col_side = 0) {
+  const size_t off = static_cast<size_t>(EDGE ? adj_row<BC>(r, g.ny) : r) * g.ld;
+  const bool ghost_row = EDGE && BC != 0 && (r < 0 || r >= g.ny);
   const bool ghost = ghost_col || ghost_row;
   const int side = ghost_row ? (r < 0 ? kSouth : kNorth) : col_side;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const double x = wb[v * g.plane + off];
+    // (a uniform base and a 32-bit column: no address arithmetic per lane)
+    const double x = (wb + v * g.plane + off)[col];
     w[v] = (BC == kDirichlet && ghost) ? gh[side * kMaxVar + v] : x;
-    const double y = lb[v * g.plane + off];
+    const double y = (lb + v * g.plane + off)[col];
     l[v] = ghost ? 0.0 : y;
   }
 }
@@ -203,8 +256,10 @@ __device__ __forceinline__ void load_adj_row(double* w, double* l, const double*
 // the rows they share (one's last row, the other's halo row) at about the
 // same time and the second read is served from L2. Every face is evaluated
 // with the same arguments and every cell sums its shares in the same order
-// in both directions, so the multipliers do not depend on it.
-template <class M, int BC, bool DOWN = false>
+// in both directions, so the multipliers do not depend on it. EDGE: the tile
+// touches the grid's boundary; an inner one leaves out the ghosts' selects and
+// shares, 72 of a row's 333 vector instructions for Euler.
+template <class M, int BC, bool DOWN = false, bool EDGE = true>
 __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a, int xs, int j0,
                                                int j1, double mux, double muy) {
   constexpr int NV = M::NV;
@@ -212,47 +267,48 @@ __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a,
   const int lane = threadIdx.x & (kWave - 1);
   const GridGeom& g = a.g;
   const int i = xs - 1 + lane;
-  const int ic = adj_col<BC>(i, g.nx);
-  const bool out = (lane >= 1) & (lane <= kOutPerWave) & (i < g.nx);
-  const bool ghost_col = BC != 0 && (i < 0 || i >= g.nx);
+  const unsigned int ic = static_cast<unsigned int>(EDGE ? adj_col<BC>(i, g.nx) : i);
+  const bool out = (lane >= 1) & (lane <= kOutPerWave) & (!EDGE || i < g.nx);
+  const bool ghost_col = EDGE && BC != 0 && (i < 0 || i >= g.nx);
   const int col_side = i < 0 ? kWest : kEast;
   const double* gh = a.ghost;
-  const bool west = BC == 1 && i == 0;
-  const bool east = BC == 1 && i == g.nx - 1;
+  const bool west = EDGE && BC == 1 && i == 0;
+  const bool east = EDGE && BC == 1 && i == g.nx - 1;
   const double kw = west ? 2.0 : 1.0, ke = east ? 2.0 : 1.0;
-  const double* wb = a.w + ic;
-  const double* lb = a.lam_in + ic;
 
   // Register ring of R = PF + 2 rows of (W, lambda): row j in slot c, the
   // next row in the march (j + S) in slot n, rows up to PF further loading
   // into the slot the row behind vacated. The row loop is unrolled R times
   // so every slot index is static; rows past the tile are computed from
   // loads clamped to its halo row and not stored.
-  constexpr int PF = FVM_ADJ_PREFETCH;
+  constexpr int PF = M::kRowsAhead;
   constexpr int R = PF + 2;
   constexpr int S = DOWN ? -1 : 1;
   const int jf = DOWN ? j1 - 1 : j0;   // the first row of the march
   const int jh = DOWN ? j0 - 1 : j1;   // the halo row past its last
   auto ahead = [&](int r) { return DOWN ? max(r, jh) : min(r, jh); };
   auto row = [&](double* w, double* l, int r) {
-    load_adj_row<NV, BC>(w, l, wb, lb, g, r, ghost_col, gh, col_side);
+    load_adj_row<NV, BC, EDGE>(w, l, a.w, a.lam_in, g, r, ic, ghost_col, gh, col_side);
   };
   // the face behind the current row (between it and the previous one in
   // the march): lower row's share Fl, upper row's share Fu, d = lam_upper -
   // lam_lower
   double W[R][NV], L[R][NV], Fl[NV], Fu[NV], Fd[NV];
   Prim P[R];
+  typename M::Side Y[R];
   row(W[R - 1], L[R - 1], jf - S);
   row(W[0], L[0], jf);
 #pragma unroll
   for (int p = 1; p <= PF; ++p) row(W[p], L[p], ahead(jf + S * p));
   m.prim(W[R - 1], P[R - 1]);
   m.prim(W[0], P[0]);
+  m.template side<1>(P[R - 1], Y[R - 1]);
+  m.template side<1>(P[0], Y[0]);
   {
     const int lo = DOWN ? 0 : R - 1, up = DOWN ? R - 1 : 0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) Fd[v] = L[up][v] - L[lo][v];
-    m.template face<1>(W[lo], P[lo], W[up], P[up], Fd, Fl, Fu);
+    m.template face<1>(W[lo], Y[lo], W[up], Y[up], Fd, Fl, Fu);
   }
 
   for (int jb = jf; DOWN ? jb > jh : jb < jh; jb += S * R) {
@@ -262,12 +318,13 @@ __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a,
       const int c = u, n = (u + 1) % R, l = (u + R - 1) % R;
       row(W[l], L[l], ahead(j + S * (1 + PF)));
       m.prim(W[n], P[n]);
+      m.template side<1>(P[n], Y[n]);
       // the face ahead: north of row j going up, south of it going down
       double Gd[NV], Gl[NV], Gu[NV];
       const int glo = DOWN ? n : c, gup = DOWN ? c : n;
 #pragma unroll
       for (int v = 0; v < NV; ++v) Gd[v] = L[gup][v] - L[glo][v];
-      m.template face<1>(W[glo], P[glo], W[gup], P[gup], Gd, Gl, Gu);
+      m.template face<1>(W[glo], Y[glo], W[gup], Y[gup], Gd, Gl, Gu);
       // row j's north face (its lower share An, the upper Bn, dn) and south
       // face (As, Bs, ds)
       const double* An = DOWN ? Fl : Gl;
@@ -277,14 +334,15 @@ __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a,
       const double* Bs = DOWN ? Gu : Fu;
       const double* ds = DOWN ? Gd : Fd;
       double dx[NV], Wr[NV], Ax[NV], Bx[NV];
-      Prim Pr;
-      m.shift_next(W[c], P[c], Wr, Pr);
+      typename M::Side X, Xr;
+      m.template side<0>(P[c], X);
+      m.shift_next(W[c], X, Wr, Xr);
 #pragma unroll
       for (int v = 0; v < NV; ++v) dx[v] = from_next(L[c][v]) - L[c][v];
-      m.template face<0>(W[c], P[c], Wr, Pr, dx, Ax, Bx);
-      const bool south = BC == 1 && j == 0;
-      const bool north = BC == 1 && j == g.ny - 1;
-      const size_t cell = static_cast<size_t>(j) * g.ld + ic;
+      m.template face<0>(W[c], X, Wr, Xr, dx, Ax, Bx);
+      const bool south = EDGE && BC == 1 && j == 0;
+      const bool north = EDGE && BC == 1 && j == g.ny - 1;
+      const size_t line = static_cast<size_t>(j) * g.ld;
       // A(W)^T of the sums of the cell's faces' d along each axis (a
       // transmissive ghost is a copy of the cell: its face counts twice)
       double gx[NV], gy[NV];
@@ -300,12 +358,15 @@ __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a,
         m.template at_d<0>(W[c], P[c], Dx, gx);
         m.template at_d<1>(W[c], P[c], Dy, gy);
       }
+      double to[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const double bw = from_prev(Bx[v]);
-        const double aw = from_prev(Ax[v]);
         double sx = Ax[v] + bw;
-        if (west) sx += aw;
+        if constexpr (EDGE && BC == 1) {
+          const double aw = from_prev(Ax[v]);
+          if (west) sx += aw;
+        }
         if (east) sx += Bx[v];
         double sy = An[v] + Bs[v];
         if (south) sy += As[v];
@@ -314,8 +375,11 @@ __device__ __forceinline__ void adjoint_strip1(const M& m, const AdjointArgs& a,
           sx = fma(0.5, gx[v], sx);
           sy = fma(0.5, gy[v], sy);
         }
-        const double lo = L[c][v] + fma(mux, sx, muy * sy);
-        if (out && j >= j0 && j < j1) a.lam_out[v * g.plane + cell] = lo;
+        to[v] = L[c][v] + fma(mux, sx, muy * sy);
+      }
+      if (out && j >= j0 && j < j1) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) (a.lam_out + v * g.plane + line)[ic] = to[v];
       }
       // the face ahead is the next row's face behind; of its shares that
       // row needs only its own (its other face's ghost share applies at the

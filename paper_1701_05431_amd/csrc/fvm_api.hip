@@ -219,10 +219,12 @@ void default_tiling(const fvm_params& p, int cpl, int* rows, int* wpb) {
   fit_strips(strips_x, p.ny, per_cu, unroll, 128, 8, rows, wpb);
 }
 
-// The adjoint's strips: 62 columns, two waves per SIMD, four unrolled rows;
-// tiles taller than 16 rows run slower although they re-read fewer rows.
+// The adjoint's strips: 62 columns, two waves per SIMD, two unrolled rows
+// (advection four); tiles taller than 16 rows run slower although they re-read
+// fewer rows.
 void default_adjoint_tiling(const fvm_params& p, int* rows, int* wpb) {
-  fit_strips((p.nx + kOutPerWave - 1) / kOutPerWave, p.ny, 8, 4, 16, 4, rows, wpb);
+  const int unroll = p.model == FVM_EULER ? 2 : 4;
+  fit_strips((p.nx + kOutPerWave - 1) / kOutPerWave, p.ny, 8, unroll, 16, 4, rows, wpb);
 }
 
 bool valid_tiling(int rows, int wpb) {
