@@ -941,15 +941,27 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
     rc = dev_err(hipMemcpyAsync(ckpts[0], g->cur, bytes, hipMemcpyDeviceToDevice, g->stream));
     if (rc) return rc;
   }
-  if (nsteps > 0 && nck - 1 <= cluster::kMaxSaves && cluster_ok(g)) {
+  if (nsteps > 0 && cluster_ok(g)) {
+    // a launch saves so many states at most; the next goes on from the last of
+    // them (`last` holds the unsaved states where a launch cannot have the chip)
     double* last = g->other(g->cur);
-    cluster::Args a = cluster_args(g, kDtAdaptive, nsteps, g->cur, last, nullptr);
-    a.every = ckpt_every;
-    a.nsaves = nck - 1;
-    for (int s = 1; s < nck; ++s) a.saves[s - 1] = ckpts[s];
-    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
-    if (rc == FVM_OK) g->cur = last;
-    return rc;
+    const double* from = g->cur;
+    for (int s = 0;;) {
+      const int saves = std::min(nck - 1 - s, static_cast<int>(cluster::kMaxSaves));
+      const bool end = s + saves == nck - 1;
+      const int steps = end ? nsteps - s * ckpt_every : saves * ckpt_every;
+      cluster::Args a = cluster_args(g, kDtAdaptive, steps, from, last, nullptr);
+      a.every = ckpt_every;
+      a.nsaves = saves;
+      for (int q = 0; q < saves; ++q) a.saves[q] = ckpts[s + 1 + q];
+      rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+      if (rc) return rc;
+      s += saves;
+      if (end) break;
+      from = ckpts[s];
+    }
+    g->cur = last;
+    return FVM_OK;
   }
   const double* in = g->cur;
   for (int k = 0; k < nsteps; ++k) {

@@ -11,7 +11,7 @@ import pytest
 import torch
 
 from paper_1701_05431_amd import _lib, inputs
-from paper_1701_05431_amd.solver import Solver, params_from
+from paper_1701_05431_amd.solver import Solver, fvrun, params_from
 
 pytestmark = pytest.mark.gpu
 
@@ -116,6 +116,26 @@ def test_failed_checks_and_bad_states():
         s.set_state(bad)
         s.run(3)
         assert s.sync() == _lib.FVM_ENONFINITE
+
+
+@pytest.mark.parametrize("nsteps,every", [(65, 1), (66, 1), (150, 1), (131, 2), (193, 3), (194, 3)])
+def test_more_checkpoints_than_one_launch_saves(nsteps, every):
+    (a, b), _ = solvers(1, 1, 70, 90, layout=1)
+    (ca, da), (cb, db) = (s.run_ckpt(nsteps, every) for s in (a, b))
+    assert torch.equal(da, db) and len(ca) == len(cb)
+    assert all(torch.equal(x, y) for x, y in zip(ca, cb))
+    same(a, b)
+
+
+@pytest.mark.parametrize("nsteps", [1, 12])
+def test_the_default_checkpoints_change_no_gradient(nsteps):
+    (a, b), W = solvers(1, 1, 70, 90, layout=1)
+    grads = []
+    for s, every in ((a, None), (b, 4)):
+        X = torch.from_numpy(W).cuda().requires_grad_(True)
+        (fvrun(X, s, nsteps, every) ** 2).sum().backward()
+        grads.append(X.grad)
+    assert torch.equal(*grads)
 
 
 @pytest.mark.parametrize("model,every", [(1, 1), (1, 4), (2, 3), (0, 5)])
