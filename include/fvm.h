@@ -421,7 +421,7 @@ int fvm_batch_cfl(fvm_batch* b);
  * field overlaps the current buffer or is not aligned to 8 bytes. */
 int fvm_batch_load(fvm_batch* b, const double* const* src, void* stream);
 
-/* nsteps adaptive steps of every grid, one persistent launch per step
+/* nsteps adaptive steps of every grid, one launch per step
  * replayed from a cached HIP graph. dts_dev (nullable) receives
  * dts_dev[s * n + k] = dt of grid k at step s. */
 int fvm_batch_run(fvm_batch* b, int nsteps, double* dts_dev);

@@ -240,8 +240,8 @@ struct fvm_batch {
   // Short row blocks, one workgroup per item: the dispatcher balances them, and
   // an item's end costs little since its commit has no fence. Measured, us a
   // step, against blocks of 32 rows in workgroups of two waves that stay and
-  // draw from the queue: 256 grids of 64..1024 (58 M cells) 710 -> 622, 100 of
-  // 50..800 248 -> 164, 64 of 64..256 52 -> 33, 16 of 64..128 45 -> 15.
+  // draw from the queue: 256 grids of 64..1024 (58 M cells) 710 -> 600, 100 of
+  // 50..800 248 -> 161, 64 of 64..256 52 -> 34, 16 of 64..128 45 -> 15.
   int rows = 8, wpb = 4;
   bool persist = false;          // persistent workgroups or one per item
   bool fit = true;               // row blocks chosen to fill whole workgroups

@@ -3,7 +3,7 @@
 //
 // What bounds a step of such a grid when every step is its own launch is not
 // its traffic but the launch: start, first loads, the reduction's chain of
-// device atomics, the next launch (10 us a step for 200 x 150 cells, 24 us for
+// device atomics, the next launch (8 us a step for 200 x 150 cells, 23 us for
 // 1024^2 where 6 us of arithmetic are needed). Here up to 256 workgroups, one
 // per CU, keep their tile of the state in LDS for the whole run:
 //  - a tile is up to 62 columns wide, one column per lane, lanes 0 and
@@ -24,9 +24,9 @@
 // state k + 2 in that set can find state k - 1.
 //
 // Measured, us a step in runs of 20 to 100 steps, step launches / on the chip:
-// advection 512^2 9.6 / 5.9, 1500^2 32.6 / 8.7; Euler 200 x 150 10.4 / 5.5, 512^2
-// 13.9 / 9.0, 1024^2 23.8 / 15.3; spray 200^2 14.8 / 6.0, 512^2 17.3 / 11.7, 860 x 900
-// 33.4 / 18.9. About 5 us of each are the exchange (2 us from a store to the
+// advection 512^2 9.5 / 5.7, 1500^2 17.6 / 8.6; Euler 200 x 150 8.2 / 5.4, 512^2
+// 13.8 / 8.8, 1024^2 23.3 / 14.9; spray 200^2 10.5 / 5.9, 512^2 18.3 / 11.7, 860 x 900
+// 32.6 / 18.2. About 5 us of each are the exchange (2 us from a store to the
 // neighbour's load), the rest the arithmetic: 1.0 us a row of 8 waves for Euler.
 #pragma once
 
