@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void batch_cfl_kernel(BatchArgs a) {
 // The same for new states, which go into a.wout on the way: grids a.grids[first
 // + k], k < n, from dense (nVar, Ny, Nx) fields. The sources' addresses are
 // kernel arguments (2 KB of the 4 KB these may have), so that nothing has to be
-// uploaded or kept. 256 grids, 58 M cells: 0.60 ms, where 256 copies and the
+// uploaded or kept. 256 grids, 47 M cells: 0.60 ms, where 256 copies and the
 // maxima after them took 3.7 ms with the gaps between the copies.
 constexpr int kLoadGrids = 256;
 struct BatchSources {
@@ -240,7 +240,7 @@ struct fvm_batch {
   // Short row blocks, one workgroup per item: the dispatcher balances them, and
   // an item's end costs little since its commit has no fence. Measured, us a
   // step, against blocks of 32 rows in workgroups of two waves that stay and
-  // draw from the queue: 256 grids of 64..1024 (58 M cells) 710 -> 600, 100 of
+  // draw from the queue: 256 grids of 64..1024 (47 M cells) 710 -> 600, 100 of
   // 50..800 248 -> 161, 64 of 64..256 52 -> 34, 16 of 64..128 45 -> 15.
   int rows = 8, wpb = 4;
   bool persist = false;          // persistent workgroups or one per item

@@ -521,8 +521,11 @@ class FVRun(torch.autograd.Function):
     def forward(ctx, W0, solver: Solver, nsteps: int, every: int):
         solver.set_state(W0.detach())
         nck = (nsteps + every - 1) // every
-        ck = torch.empty((nck,) + tuple(solver.wa.shape), dtype=torch.float64,
-                         device=solver.device).unbind(0)
+        try:  # one allocation, not one a state
+            ck = torch.empty((nck,) + tuple(solver.wa.shape), dtype=torch.float64,
+                             device=solver.device).unbind(0)
+        except torch.cuda.OutOfMemoryError:  # not in one piece
+            ck = [torch.empty_like(solver.wa) for _ in range(nck)]
         ck, dts = solver._run_ckpt(nsteps, every, ck)
         ctx.solver = solver
         ctx.every = every
