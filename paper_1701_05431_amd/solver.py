@@ -83,6 +83,7 @@ class Solver:
         self.p = p
         self.device = torch.device(device)
         self.nv = L.fvm_nvar(p.model)
+        self.memory = torch.cuda.get_device_properties(self.device).total_memory
         shape = storage_shape(p, self.nv)
         self.wa = torch.zeros(shape, dtype=torch.float64, device=self.device)
         self.wb = torch.zeros(shape, dtype=torch.float64, device=self.device)
@@ -545,16 +546,19 @@ def _ckpt_every(solver: Solver, nsteps: int) -> int:
     the fewest states, about 2 sqrt(nsteps), and computes nearly every step
     twice. States are kept more often, up to every one, as far as those of the
     run take at most a hundredth of the device's memory and half of that memory
-    is free of tensors (many runs may wait for their backward pass): 50 steps of
+    is free (many runs may wait for their backward pass; asking takes time, so a
+    run of less than a ten thousandth does not): 50 steps of
     1024^2 Euler and their gradient, every state kept (1.7 GB of 288), take 2256 us
     instead of 3000, 16 steps of 512^2 spray 549 instead of 746."""
     every = max(1, int(round(math.sqrt(nsteps))))
-    memory = torch.cuda.get_device_properties(solver.wa.device).total_memory
-    if torch.cuda.memory_allocated(solver.wa.device) > memory // 2:
-        return every
-    state = 8 * solver.wa.numel()
+    memory, state = solver.memory, 8 * solver.wa.numel()
     for e in range(1, every):
-        if state * (-(-nsteps // e) + e) <= memory // 100:
+        states = state * (-(-nsteps // e) + e)
+        if states <= memory // 100:
+            if states > memory // 10000:
+                free, _ = torch.cuda.mem_get_info(solver.wa.device)
+                if free < memory // 2:
+                    return every
             return e
     return every
 
