@@ -270,7 +270,11 @@ int fvm_run_noalloc(const fvm_params* p, double* w_a, double* w_b,
 /* Waits for the stream and returns the sticky device status. */
 int fvm_sync(fvm_grid* g);
 
-/* Waits, then returns the sticky device status (and clears it if clear != 0). */
+/* Waits, then returns the sticky device status (and clears it if clear != 0).
+ * FVM_EDEVICE from the device means that a run on the chip (see
+ * fvm_set_resident_runs) ran out of time: the state is then unspecified, and
+ * runs on the chip report the error again until it has been cleared here;
+ * after that a new state can be set and run. */
 int fvm_get_status(fvm_grid* g, int clear);
 
 /* Gradient of a loss of the final state with respect to the initial state,

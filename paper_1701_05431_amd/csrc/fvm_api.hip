@@ -659,7 +659,15 @@ int fvm_get_status(fvm_grid* g, int clear) {
   int rc = read_scratch(g, &h);
   if (rc) return rc;
   rc = status_from_bits(h.status);
-  if (clear && h.status) {
+  if (clear && (h.status & kStatusWait)) {
+    // a run on the chip broke off: its counts and exchange words go too
+    hipError_t e = cluster::launch_clear_area(g->scr, cluster::area_words(g->nv, g->plan),
+                                              g->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
+    g->speeds_valid = false;
+    g->log_armed = nullptr;
+    if (e != hipSuccess) return FVM_EDEVICE;
+  } else if (clear && h.status) {
     const unsigned int zero = 0;
     const hipError_t e = hipMemcpy(&g->scr->status, &zero, sizeof(zero), hipMemcpyHostToDevice);
     if (e != hipSuccess) return FVM_EDEVICE;

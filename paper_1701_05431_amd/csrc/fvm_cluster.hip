@@ -9,7 +9,9 @@
 // workgroup that waits for nobody. After "go" every workgroup is resident and
 // stays until the run is over, so every later wait is for something that is on
 // its way; those waits are bounded all the same (kWaitLimit), and running out
-// is reported as a device error.
+// is reported as a device error. Such a run leaves its words and counts behind
+// (`abort` says so): no run starts on them, each reports the error again, until
+// the host has emptied them (fvm_get_status with clear, fvm_bind).
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -63,7 +65,12 @@ __device__ __forceinline__ bool await(const u64* const* p, Control* ctl, u64* v)
 }
 
 // All workgroups are resident (true), or nobody runs (false): thread 0 only.
-__device__ inline bool all_started(Control* ctl, u64 tiles) {
+// (`abort` cannot come from this run yet: a wait follows the last arrival.)
+__device__ inline bool all_started(Control* ctl, u64 tiles, GridScratch* s) {
+  if (peek(&ctl->abort) != 0) {
+    atomicOr(&s->status, kStatusWait);
+    return false;
+  }
   const u64 n = __hip_atomic_fetch_add(&ctl->arrived, 1ull, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
   u64 open = 0;
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid & (kWave - 1), wave = wave_index();
   const int tile = static_cast<int>(blockIdx.x);
-  if (tid == 0) s_ok = all_started(ctl, static_cast<u64>(P.tiles)) ? 1 : 0;
+  if (tid == 0) s_ok = all_started(ctl, static_cast<u64>(P.tiles), a.scr) ? 1 : 0;
   __syncthreads();
   if (!s_ok) return;
 
@@ -428,7 +435,7 @@ template <class M, int BC>
 __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
   constexpr int NV = M::NV, kThreads = kGeneralThreads, kWaves = kThreads / kWave;
   Control* const ctl = reinterpret_cast<Control*>(a.area);
-  if (peek(&ctl->decision) != 2) return;
+  if (peek(&ctl->decision) != 2 || peek(&ctl->abort) != 0) return;
   __shared__ u64 s_red[2][kWaves];
   const M m(a.m);
   const GridGeom& g = a.g;

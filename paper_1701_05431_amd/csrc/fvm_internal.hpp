@@ -29,7 +29,7 @@ enum : unsigned int {
   kStatusNonFinite = 1u,  // NaN/inf speed or a non-physical cell
   kStatusCfl = 2u,        // fixed-dt step failed the CFL check
   kStatusDt = 4u,         // adaptive dt not positive (all speeds zero, no dt_max)
-  kStatusWait = 8u,       // a register-resident run ran out of time waiting for a tile
+  kStatusWait = 8u,       // a run on the chip ran out of time waiting for a tile
 };
 
 // Time-step source of a step launch.

@@ -180,3 +180,37 @@ def test_a_chosen_strip_shape_still_runs_strips():
     a.run(4)
     b.run(4)
     same(a, b)
+
+
+def control(s, area=False):
+    """The words in front of the exchange area (workgroups started, decision,
+    workgroups done, a wait ran out), or the area behind them."""
+    words = s.scratch_view.view(torch.int64)[32:]
+    return words[32:] if area else words[:32]
+
+
+@pytest.mark.parametrize("model,nx,ny", [(0, 150, 130), (1, 200, 150), (2, 130, 70)])
+def test_a_run_that_broke_off_is_not_built_upon(model, nx, ny):
+    """What a run leaves behind when a wait runs out, written from the host:
+    counts part of the way, words that hold a state. No run takes them for its
+    own, and after the status has been cleared the grid runs as a new one."""
+    (a, b), W = solvers(model, 1, nx, ny, layout=1)
+    empty = control(a, area=True).clone()
+    used = empty != 0  # (not what rounds the scratch up to 256 bytes)
+    for steps in (4, 5):
+        a.run(4)
+        torch.cuda.synchronize()
+        control(a, area=True).copy_(torch.tensor(0.25, dtype=torch.float64).view(torch.int64))
+        control(a)[:4] = torch.tensor([7, 1, 3, 1], device="cuda")
+        for _ in range(2):
+            a.set_state(W)
+            a.run(4)
+            assert a.sync() == _lib.FVM_EDEVICE
+        assert a.status(clear=True) == _lib.FVM_EDEVICE
+        assert a.sync() == 0
+        assert torch.equal(control(a, area=True)[used], empty[used])
+        for s in (a, b):
+            s.set_state(W)
+        da, db = a.run(steps, record_dt=True), b.run(steps, record_dt=True)
+        assert torch.equal(da, db)
+        same(a, b)
