@@ -254,12 +254,13 @@ size_t cluster_bytes(const fvm_params& p) {
 }
 
 // Two such runs at once, from two streams, could each hold some of the CUs
-// and wait for the rest; the second waits for the first instead. One event
-// per device, kept until the process ends.
+// and wait for the rest; the second waits for the first instead, also where the
+// handles of their streams are equal (hipStreamPerThread names a stream per
+// thread, and a destroyed stream's handle may be another's by now). One event per
+// device, kept until the process ends.
 struct ClusterTurn {
   std::mutex mu;
   hipEvent_t ended = nullptr;
-  hipStream_t stream = nullptr;
 };
 constexpr int kTurnDevices = 64;
 ClusterTurn g_turn[kTurnDevices];
@@ -270,12 +271,11 @@ hipError_t launch_in_turn(const cluster::Args& a, int model, int device, hipStre
   hipError_t e = hipSuccess;
   if (!t.ended) {
     e = hipEventCreateWithFlags(&t.ended, hipEventDisableTiming);
-  } else if (t.stream != st) {
+  } else {
     e = hipStreamWaitEvent(st, t.ended, 0);
   }
   if (e == hipSuccess) e = cluster::launch_run(a, model, st);
   if (e == hipSuccess) e = hipEventRecord(t.ended, st);
-  t.stream = st;
   return e;
 }
 

@@ -1,0 +1,96 @@
+"""What the host asks of the runtime for runs that keep the state on the chip,
+without a GPU: the library runs in a child process on stand-ins of the HIP calls
+(tests/emu/hip_calls.cpp) that log every launch, event record and wait. Such
+runs wait for all of their workgroups to be resident, so runs that are not
+ordered by events must fit the chip together, whatever the handles of their
+streams say: a handle may name another stream than the one it named before."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+# argv: the stand-ins, a list of actions; prints the log as lists, one per action
+CHILD = """
+import ctypes as C, json, sys
+stub = C.CDLL(sys.argv[1])
+stub.calls_log.restype = C.c_char_p
+from paper_1701_05431_amd import _lib
+L = _lib.lib()
+grids, logs = {}, []
+def grid(name, nx, ny, stream=0, model=1):
+    p = _lib.Params(model=model, bc=1, nx=nx, ny=ny, npart_x=1, npart_y=1, ld=nx, layout=0,
+                    lx=1.0, ly=1.0, gamma=1.4, ax=1.0, ay=0.5, cfl=0.4)
+    h = C.c_void_p()
+    code = L.fvm_create(C.byref(p), C.byref(h))
+    at = 4096 * (1 + 10 * len(grids))  # never looked at: nothing runs
+    grids[name] = h
+    return code or L.fvm_bind(h, at, at + 4096, None, at + 8192, stream)
+def run(name, steps=20):
+    return L.fvm_run_dts(grids[name], steps, 8)
+def stream(name, s):
+    return L.fvm_set_stream(grids[name], s)
+def device(d):
+    return stub.calls_device(d) and 0
+for f, *args in json.loads(sys.argv[2]):
+    stub.calls_clear()
+    code = globals()[f](*args) if f in ("grid", "run", "stream", "device") else \\
+        getattr(L, f)(grids[args[0]], *args[1:])
+    log = [q.split() for q in stub.calls_log().decode().splitlines()]
+    logs.append([code, [[q[0]] + [int(x) for x in q[1:]] for q in log]])
+print(json.dumps(logs))
+"""
+
+
+@pytest.fixture(scope="module")
+def calls(tmp_path_factory):
+    from paper_1701_05431_amd import _lib
+    if not os.path.exists(CLANG):
+        pytest.skip("needs the ROCm clang++ for a host build")
+    if not os.path.exists(_lib.LIB_PATH):
+        from paper_1701_05431_amd import build
+        build.build()
+    so = str(tmp_path_factory.mktemp("calls") / "hip_calls.so")
+    subprocess.run([CLANG, "-std=c++17", "-O1", "-shared", "-fPIC",
+                    os.path.join(ROOT, "tests", "emu", "hip_calls.cpp"), "-o", so], check=True)
+
+    def do(*actions):
+        first = os.environ.get("LD_PRELOAD")
+        env = dict(os.environ, LD_PRELOAD=so + (":" + first if first else ""))
+        out = subprocess.run([sys.executable, "-c", CHILD, so, json.dumps(actions)], cwd=ROOT,
+                             env=env, check=True, capture_output=True, text=True, timeout=120)
+        return json.loads(out.stdout.splitlines()[-1])
+
+    return do
+
+
+def turns(results):
+    """The runs of one log an action, in order: [(tiles, ordered after)]."""
+    runs, done = [], {}
+    for code, log in results:
+        assert code == 0, results
+        launches = [q for q in log if q[0] == "launch"]
+        after = set()
+        for what, a, b, _ in log:
+            if what == "wait":
+                after |= done.get(a, set())
+            if what == "record":
+                done[a] = after | {len(runs)}
+        if launches:
+            first = next(i for i, q in enumerate(log) if q[0] == "launch")
+            assert all(q[0] != "wait" for q in log[first:]), log
+            assert log[-1][0] == "record", log
+            runs.append((launches[0][1], after))
+    return runs
+
+
+def test_equal_stream_handles_are_not_the_same_stream(calls):
+    """Two runs of the whole chip from one handle: hipStreamPerThread (2) of two
+    threads, or a stream made where a destroyed one was."""
+    setup = [("grid", "a", 1024, 1024, 2), ("grid", "b", 1000, 1000, 2)]
+    got = calls(*setup, ("run", "a"), ("run", "b"), ("run", "a"))[2:]
+    assert [r[1] for r in turns(got)] == [set(), {0}, {0, 1}]
