@@ -319,7 +319,7 @@ struct fvm_grid {
   bool plan_ok = false;
   bool default_strips = true;  // rows and wpb are the default for the layout
   bool strips_asked = false;  // the caller chose a strip shape: its runs are step launches
-  int device = -1;
+  int device = -1;       // current at bind, -1 if it cannot hold the plan's tiles at once
   int cpl = 1;       // layout in use
   double* w_a = nullptr;
   double* w_b = nullptr;
@@ -827,10 +827,15 @@ static bool resident_ok(const fvm_grid* g) {
 }
 
 // A run of steps can keep the state in the LDS of all CUs: the grid fits, no
-// halo rows, the caller has not asked for a strip shape, and the stream is not
-// being captured (the launch may have to wait for another stream's).
+// halo rows, the caller has not asked for a strip shape, the stream is one of the
+// grid's device, which is the current one (the turns' events are its own), and
+// is not being captured (the launch may have to wait for another stream's).
 static bool cluster_ok(const fvm_grid* g) {
   if (!g->resident || !g->plan_ok || g->device < 0 || g->strips_asked || g->halo.s || g->halo.n)
+    return false;
+  int dev = -1, sdev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(g->stream, &sdev) != hipSuccess ||
+      dev != g->device || sdev != g->device)
     return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(g->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;

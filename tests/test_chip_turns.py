@@ -94,3 +94,18 @@ def test_equal_stream_handles_are_not_the_same_stream(calls):
     setup = [("grid", "a", 1024, 1024, 2), ("grid", "b", 1000, 1000, 2)]
     got = calls(*setup, ("run", "a"), ("run", "b"), ("run", "a"))[2:]
     assert [r[1] for r in turns(got)] == [set(), {0}, {0, 1}]
+
+
+def test_runs_stay_off_the_chip_on_another_devices_stream(calls):
+    """A stream of another device than the grid's, or another current device:
+    the steps are launches on the stream, as without runs on the chip."""
+    one, other = 0x00002, 0x10002  # streams of devices 0 and 1
+    got = calls(("grid", "a", 1024, 1024, one), ("run", "a"), ("stream", "a", other), ("run", "a"),
+                ("device", 1), ("run", "a"), ("stream", "a", one), ("run", "a"), ("device", 0),
+                ("run", "a"))
+    assert all(code == 0 for code, _ in got)
+    steps = [[q[0] for q in log] for (code, log), f in
+             zip(got, "grid run stream run device run stream run device run".split()) if f == "run"]
+    chip, launches = ["launch", "launch", "record"], ["graph"]
+    assert steps[0] == chip and steps[4] == ["wait"] + chip
+    assert steps[1] == steps[2] == steps[3] == launches
