@@ -356,10 +356,13 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *    of fvm_adjoint_run on a grid that up to 256 tiles of 62 columns and 300
  *    (advection), 76 (Euler) or 50 (spray) rows cover, e.g. 1024 x 1024 Euler,
  *    run on up to 256 workgroups that exchange their tiles' edges, unless the
- *    caller has chosen a strip shape (fvm_set_tiling, fvm_set_cells_per_lane) or
- *    the stream is being captured. Such runs wait for each other across the
- *    streams of a process; should the workgroups not all become resident (the
- *    device is shared with another process's), one workgroup makes the run.
+ *    caller has chosen a strip shape (fvm_set_tiling, fvm_set_cells_per_lane),
+ *    the stream is being captured or the stream is another device's than the
+ *    grid's or the current one. Such runs on different streams of a process go
+ *    on side by side where they fit the chip together, counted in eighths of it
+ *    (32 tiles); otherwise a run waits for the earlier ones. Should the
+ *    workgroups not all become resident (the device is shared with another
+ *    process's), one workgroup makes the run.
  * States, dts, the dt log, the maxima and the status are bitwise those of
  * the step launches; the other ping-pong buffer ends up holding the state
  * before the last step, as with step launches (fvm_run, fvm_run_fixed,

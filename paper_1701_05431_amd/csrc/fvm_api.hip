@@ -254,29 +254,69 @@ size_t cluster_bytes(const fvm_params& p) {
 }
 
 // Two such runs at once, from two streams, could each hold some of the CUs
-// and wait for the rest; the second waits for the first instead, also where the
-// handles of their streams are equal (hipStreamPerThread names a stream per
-// thread, and a destroyed stream's handle may be another's by now). One event per
-// device, kept until the process ends.
+// and wait for the rest, so unordered runs have to fit the chip together. The
+// chip is handed out in parts of 32 CUs: a run takes as many parts as its tiles
+// fill and waits for the runs that had them before; runs of small grids on other
+// streams go on beside it (us for a run(50) on each of 8 streams, in parts / one
+// run at a time / as step launches: Euler 64^2 532 / 2010 / 1148, 200 x 150 1140 /
+// 2178 / 1383, spray 200^2 1330 / 2429 / 1969). A stream is given the parts it had
+// before, then the ones not used for longest. That is no more than a choice: the
+// wait is made also where the handles of two streams are equal
+// (hipStreamPerThread names a stream per thread, and a destroyed stream's handle
+// may be another's by now). One event per part and device, kept until the
+// process ends.
+constexpr int kParts = 8;
+constexpr int kPartTiles = cluster::kMaxTiles / kParts;
+struct ChipPart {
+  hipEvent_t event = nullptr;   // its own
+  hipEvent_t ended = nullptr;   // end of its last run, a part's event: a run over
+                                // several parts records its first one's
+  hipStream_t stream = nullptr;
+  unsigned long long used = 0;  // number of the last run, 0: none
+};
 struct ClusterTurn {
   std::mutex mu;
-  hipEvent_t ended = nullptr;
+  ChipPart part[kParts];
+  unsigned long long runs = 0;
 };
 constexpr int kTurnDevices = 64;
 ClusterTurn g_turn[kTurnDevices];
 
-hipError_t launch_in_turn(const cluster::Args& a, int model, int device, hipStream_t st) {
+int parts_of(int cus) { return std::min(cus / kPartTiles, kParts); }
+int parts_for(const cluster::Plan& p) { return (p.tiles + kPartTiles - 1) / kPartTiles; }
+
+hipError_t launch_in_turn(const cluster::Args& a, int model, int device, int cus,
+                          hipStream_t st) {
   ClusterTurn& t = g_turn[device];
   std::lock_guard<std::mutex> lock(t.mu);
+  const int parts = parts_of(cus), n = parts_for(a.plan);
+  if (n > parts) return hipErrorInvalidValue;
+  ChipPart* order[kParts];
+  for (int k = 0; k < parts; ++k) order[k] = &t.part[k];
+  std::stable_sort(order, order + parts, [st](const ChipPart* x, const ChipPart* y) {
+    const bool mx = x->used && x->stream == st, my = y->used && y->stream == st;
+    return mx != my ? mx : x->used < y->used;
+  });
   hipError_t e = hipSuccess;
-  if (!t.ended) {
-    e = hipEventCreateWithFlags(&t.ended, hipEventDisableTiming);
-  } else {
-    e = hipStreamWaitEvent(st, t.ended, 0);
+  if (!order[0]->event) e = hipEventCreateWithFlags(&order[0]->event, hipEventDisableTiming);
+  for (int k = 0; k < n && e == hipSuccess; ++k) {
+    bool waited = !order[k]->used;
+    for (int q = 0; q < k; ++q) waited = waited || order[q]->ended == order[k]->ended;
+    if (!waited) e = hipStreamWaitEvent(st, order[k]->ended, 0);
   }
-  if (e == hipSuccess) e = cluster::launch_run(a, model, st);
-  if (e == hipSuccess) e = hipEventRecord(t.ended, st);
-  return e;
+  if (e != hipSuccess) return e;
+  e = cluster::launch_run(a, model, st);
+  if (e != hipSuccess) return e;
+  // (without its event the run must be over before the parts are given away)
+  hipEvent_t ended = order[0]->event;
+  if (hipEventRecord(ended, st) != hipSuccess) return hipStreamSynchronize(st);
+  ++t.runs;
+  for (int k = 0; k < n; ++k) {
+    order[k]->ended = ended;
+    order[k]->stream = st;
+    order[k]->used = t.runs;
+  }
+  return hipSuccess;
 }
 
 struct GraphKey {
@@ -320,6 +360,7 @@ struct fvm_grid {
   bool default_strips = true;  // rows and wpb are the default for the layout
   bool strips_asked = false;  // the caller chose a strip shape: its runs are step launches
   int device = -1;       // current at bind, -1 if it cannot hold the plan's tiles at once
+  int cus = 0;           // .. its CUs
   int cpl = 1;       // layout in use
   double* w_a = nullptr;
   double* w_b = nullptr;
@@ -465,11 +506,11 @@ int fvm_bind(fvm_grid* g, double* w_a, double* w_b, const double* ug, void* scra
   g->me_valid = false;
   g->log_armed = nullptr;
   if (g->plan_ok) {  // one workgroup of a run per CU, all of them at once
-    int cus = 0;
     if (hipGetDevice(&g->device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess)
+        hipDeviceGetAttribute(&g->cus, hipDeviceAttributeMultiprocessorCount, g->device) !=
+            hipSuccess)
       return FVM_EDEVICE;
-    if (g->device >= kTurnDevices || cus < g->plan.tiles) g->device = -1;
+    if (g->device >= kTurnDevices || parts_of(g->cus) < parts_for(g->plan)) g->device = -1;
     return dev_err(
         cluster::launch_clear_area(g->scr, cluster::area_words(g->nv, g->plan), g->stream));
   }
@@ -895,7 +936,7 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
         g->other(last));
     a.dts = dts;
     a.dt_arg = dt;
-    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
     if (rc) return rc;
     g->cur = last;
     g->speeds_valid = true;
@@ -967,7 +1008,7 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
       a.every = ckpt_every;
       a.nsaves = saves;
       for (int q = 0; q < saves; ++q) a.saves[q] = ckpts[s + 1 + q];
-      rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+      rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
       if (rc) return rc;
       s += saves;
       if (end) break;
@@ -1418,7 +1459,7 @@ int fvm_adjoint_run(fvm_grid* g, double* const* ckpts, int ckpt_every, const dou
       a.every = 1;
       a.nsaves = a.nsteps;
       for (int q = 0; q < a.nsaves; ++q) a.saves[q] = seg_buf + static_cast<size_t>(q) * state;
-      const int rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->stream));
+      const int rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
       if (rc) return rc;
       k = k1;
     }

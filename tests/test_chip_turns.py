@@ -109,3 +109,42 @@ def test_runs_stay_off_the_chip_on_another_devices_stream(calls):
     chip, launches = ["launch", "launch", "record"], ["graph"]
     assert steps[0] == chip and steps[4] == ["wait"] + chip
     assert steps[1] == steps[2] == steps[3] == launches
+
+
+def width(after, tiles):
+    """The most CUs that runs unordered with each other can want at once."""
+    n = len(tiles)
+    best = 0
+    for pick in range(1, 1 << n):
+        k = [i for i in range(n) if pick >> i & 1]
+        if not any(i in after[j] for i in k for j in k):
+            best = max(best, sum(tiles[i] for i in k))
+    return best
+
+
+def test_small_grids_on_many_streams_run_side_by_side(calls):
+    streams = range(2, 10)
+    got = calls(*[("grid", str(s), 64, 64, s) for s in streams],
+                *[("run", str(s)) for s in streams], *[("run", str(s)) for s in streams])
+    runs = turns(got[len(streams):])
+    # a stream waits for its own runs only
+    assert [r[1] for r in runs] == [set()] * 8 + [{k} for k in range(8)]
+
+
+@pytest.mark.parametrize("sizes", [[(1024, 1024), (64, 64), (200, 150), (1024, 1024), (64, 64)],
+                                   [(200, 150)] * 6, [(300, 300), (64, 64), (700, 400)],
+                                   [(130, 96), (64, 64), (512, 512)]])
+def test_unordered_runs_fit_the_chip_together(calls, sizes):
+    """Streams taking runs in turn, each stream a handle of its own or all of
+    them one: by the events alone, never more tiles at once than the chip has
+    CUs."""
+    n = len(sizes)
+    order = [(3 * k * k + k) % n for k in range(10)]
+    for same in (False, True):
+        grids = [("grid", str(k), nx, ny, 2 if same else 2 + k) for k, (nx, ny) in enumerate(sizes)]
+        runs = turns(calls(*grids, *[("run", str(k)) for k in order])[n:])
+        after = [set(r[1]) for r in runs]
+        for a in after:
+            for k in list(a):
+                a |= after[k]
+        assert 0 < width(after, [r[0] for r in runs]) <= 256

@@ -174,6 +174,22 @@ def test_two_grids_on_two_streams():
     same(b, rb)
 
 
+def test_small_and_large_grids_on_many_streams():
+    """Runs side by side, and large ones that wait for all of them."""
+    sizes = [(1, 64, 64), (1, 200, 150), (2, 90, 60), (1, 1024, 1024), (0, 130, 96), (1, 64, 65)]
+    pairs = [solvers(m, 0, nx, ny)[0] for m, nx, ny in sizes]
+    streams = [torch.cuda.Stream() for _ in sizes]
+    torch.cuda.synchronize()
+    for k in range(6):
+        for (a, _), q in zip(pairs, streams):
+            with torch.cuda.stream(q):
+                a.run(3 + k)
+    torch.cuda.synchronize()
+    for a, b in pairs:
+        b.run(sum(3 + k for k in range(6)))
+        same(a, b)
+
+
 def test_a_chosen_strip_shape_still_runs_strips():
     (a, b), _ = solvers(1, 1, 200, 150)
     a.set_tiling(8, 2)
