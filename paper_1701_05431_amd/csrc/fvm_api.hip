@@ -997,13 +997,16 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
   }
   if (nsteps > 0 && cluster_ok(g)) {
     // a launch saves so many states at most; the next goes on from the last of
-    // them (`last` holds the unsaved states where a launch cannot have the chip)
-    double* last = g->other(g->cur);
+    // them (where a launch cannot have the chip, `last` and the other buffer hold
+    // the unsaved states in turn, the current one first: `last` by the parity of
+    // the first launch's steps)
+    double* last = nullptr;
     const double* from = g->cur;
     for (int s = 0;;) {
       const int saves = std::min(nck - 1 - s, static_cast<int>(cluster::kMaxSaves));
       const bool end = s + saves == nck - 1;
       const int steps = end ? nsteps - s * ckpt_every : saves * ckpt_every;
+      if (!last) last = steps % 2 ? g->other(g->cur) : g->cur;
       cluster::Args a = cluster_args(g, kDtAdaptive, steps, from, last, nullptr);
       a.every = ckpt_every;
       a.nsaves = saves;

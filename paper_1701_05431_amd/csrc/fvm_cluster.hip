@@ -5,8 +5,8 @@
 // find out first: each counts itself in, and the last one decides "go"; a
 // workgroup that has waited for kStartLimit decides "no go", which of the two
 // comes first stands, and on "no go" everybody leaves without having touched
-// anything. The general kernel launched behind it then makes the run with one
-// workgroup that waits for nobody. After "go" every workgroup is resident and
+// anything. The general kernel launched behind it then makes the run through
+// device memory, with as many workgroups as there is room for. After "go" every workgroup is resident and
 // stays until the run is over, so every later wait is for something that is on
 // its way; those waits are bounded all the same (kWaitLimit), and running out
 // is reported as a device error. Such a run leaves its words and counts behind
@@ -27,7 +27,10 @@ namespace cluster {
 
 namespace {
 
-constexpr long long kStartLimit = 2000000;    // 20 ms of the 100 MHz clock
+// 2 ms of the 100 MHz clock: the workgroups of a run start within some 10 us of
+// each other, or when the kernel that fills the chip has ended (200 us for steps of
+// 4096^2 on another stream); a run by tickets costs 50 us a step more.
+constexpr long long kStartLimit = 200000;
 constexpr long long kWaitLimit = 400000000;   // 4 s
 
 // Words other workgroups write or read while the kernel runs: device-scope
@@ -87,6 +90,22 @@ __device__ inline bool all_started(Control* ctl, u64 tiles, GridScratch* s) {
     }
   }
   return d == 1;
+}
+
+// The first `steps` steps of a run by tickets are done (true), or time is up:
+// thread 0 only.
+__device__ inline bool steps_done(Control* ctl, u64 steps) {
+  const long long t0 = wall_clock64();
+  while (peek(&ctl->steps) < steps) {
+    if (wall_clock64() - t0 > kWaitLimit || peek(&ctl->abort) != 0) {
+      put(&ctl->abort, 1);
+      return false;
+    }
+  }
+  return true;
+}
+__device__ __forceinline__ double value(u64 word) {
+  return __longlong_as_double(static_cast<long long>(word));
 }
 
 template <class M, int BC>
@@ -427,29 +446,38 @@ __global__ __launch_bounds__(waves(M::NV) * kWave) void cluster_run_kernel(Args 
   }
 }
 
-// The same run by one workgroup that waits for nobody, through device memory;
-// runs only if the tiles could not all start.
-constexpr int kGeneralThreads = 512;
-
+// The same run where the tiles could not all start (`decision` is 2, else it
+// leaves at once), through device memory and by whatever workgroups do start. Each
+// takes the next ticket, a piece of a step's cells; tickets are numbered step by
+// step, so a workgroup waits only for pieces of earlier tickets, and those are
+// with workgroups that run. However few of them the chip has room for, the one
+// with the lowest open ticket waits for nobody. The cells of a step are seen by
+// the next through fences at device scope on both sides of the count of the
+// finished pieces; the last piece of a step takes its maxima and the next dt.
+// us a step in runs of five with their start, this / in one workgroup, as before:
+// Euler 200 x 150 22 / 124, 512^2 64 / 1179, 1024^2 80 / 4722, spray 200^2 27 / 208,
+// advection 1500^2 69 / 2674.
 template <class M, int BC>
-__global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
+__global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a, Pieces pieces) {
   constexpr int NV = M::NV, kThreads = kGeneralThreads, kWaves = kThreads / kWave;
   Control* const ctl = reinterpret_cast<Control*>(a.area);
-  if (peek(&ctl->decision) != 2 || peek(&ctl->abort) != 0) return;
   __shared__ u64 s_red[2][kWaves];
+  __shared__ u64 s_ticket;
+  __shared__ int s_run, s_go;
+  const int tid = static_cast<int>(threadIdx.x);
+  if (tid == 0) s_run = peek(&ctl->decision) == 2 && peek(&ctl->abort) == 0;
+  __syncthreads();
+  if (!s_run) return;
   const M m(a.m);
   const GridGeom& g = a.g;
   GridScratch* const s = a.scr;
-  const int tid = static_cast<int>(threadIdx.x);
   const long long ncell = static_cast<long long>(g.nx) * g.ny;
+  const u64 per_step = static_cast<u64>(pieces.count);
+  const u64 total = per_step * static_cast<u64>(a.nsteps);
   const Spacings h(g);
-  double dtn = s->dt;  // adaptive dt of the current state
-  double sx = s->cur_sx, sy = s->cur_sy;
   double* const log = s->log;
   const unsigned int log_n = s->nstep, log_cap = static_cast<unsigned int>(s->log_cap);
   const size_t log_stride = static_cast<size_t>(s->log_stride);
-  unsigned int status = 0;
-  const double* in = a.win;
   auto load = [&](const double* w, int j, int i, double* o) {
     if (BC == kDirichlet && (i < 0 || i >= g.nx || j < 0 || j >= g.ny)) {
       const int side = i < 0 ? kWest : (i >= g.nx ? kEast : (j < 0 ? kSouth : kNorth));
@@ -461,22 +489,41 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) o[v] = w[v * g.plane + at];
   };
-  for (int k = 0; k < a.nsteps; ++k) {
-    double* out = saved(a, k + 1);
-    // the last state goes to w_last, the one before it to w_prev where given
-    const bool last = k + 1 == a.nsteps;
-    if (!out) out = last && a.w_last ? a.w_last : (in == a.w_last ? a.spare : a.w_last);
-    if (out == in) out = a.spare;
+  for (;;) {
+    if (tid == 0) {
+      s_ticket = __hip_atomic_fetch_add(&ctl->ticket, 1ull, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+      s_go = s_ticket >= total ? 0 : (steps_done(ctl, s_ticket / per_step) ? 1 : 2);
+    }
+    __syncthreads();
+    const u64 ticket = s_ticket;
+    if (s_go == 0) break;  // uniform
+    if (s_go == 2) {       // uniform: a wait ran out of time
+      if (tid == 0) atomicOr(&s->status, kStatusWait);
+      return;
+    }
+    __threadfence();  // the cells of state k as their writers left them
+    const int k = static_cast<int>(ticket / per_step);
+    const long long piece = static_cast<long long>(ticket % per_step);
+    const double sx = k == 0 ? s->cur_sx : value(peek(&ctl->sx));
+    const double sy = k == 0 ? s->cur_sy : value(peek(&ctl->sy));
+    const double dtn = k == 0 ? s->dt : value(peek(&ctl->dt));
+    const double* const in = k == 0 ? a.win : state_buffer(a, k);
+    double* const out = state_buffer(a, k + 1);
+    // the last state goes to w_last, also where it is saved
+    double* const copy = k + 1 == a.nsteps && a.w_last != out ? a.w_last : nullptr;
     bool cfl_ok;
     const double used = step_dt(a, k, sx, sy, dtn, cfl_ok);
     const double dt = cfl_ok ? used : 0.0;
-    if (!cfl_ok) status |= kStatusCfl;
-    if (tid == 0 && log && log_n + k < log_cap)
-      log[static_cast<size_t>(log_n + k) * log_stride] = dt;
+    if (tid == 0 && piece == 0) {
+      if (!cfl_ok) atomicOr(&s->status, kStatusCfl);
+      if (log && log_n + k < log_cap) log[static_cast<size_t>(log_n + k) * log_stride] = dt;
+    }
     double mux, muy;
     h.courant(dt, mux, muy);
     u64 bx = 0, by = 0;
-    for (long long c = tid; c < ncell; c += kThreads) {
+    const long long end = min(ncell, (piece + 1) * pieces.cells);
+    for (long long c = piece * pieces.cells + tid; c < end; c += kThreads) {
       const int j = static_cast<int>(c / g.nx), i = static_cast<int>(c % g.nx);
       typename M::Prim P, N;
       double W[NV], X[NV], Fw[NV], Fe[NV], Gs[NV], Gn[NV], Wo[NV];
@@ -500,8 +547,12 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
         const size_t uc = ucell(g, j, i);
         m.source(Wo, a.ug[uc], a.ug[g.uplane + uc], dt);
       }
+      const size_t at = static_cast<size_t>(j) * g.ld + i;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) out[v * g.plane + static_cast<size_t>(j) * g.ld + i] = Wo[v];
+      for (int v = 0; v < NV; ++v) {
+        out[v * g.plane + at] = Wo[v];
+        if (copy) copy[v * g.plane + at] = Wo[v];
+      }
       double cx, cy;
       m.speeds(Wo, cx, cy);
       bx = umax64(bx, bits(cx));
@@ -513,36 +564,50 @@ __global__ __launch_bounds__(kGeneralThreads) void general_run_kernel(Args a) {
       s_red[0][tid / kWave] = bx;
       s_red[1][tid / kWave] = by;
     }
-    __threadfence();
+    stores_done();
     __syncthreads();
-    u64 mx = s_red[0][0], my = s_red[1][0];
+    if (tid == 0) {
+      u64 mx = s_red[0][0], my = s_red[1][0];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-      mx = umax64(mx, s_red[0][w]);
-      my = umax64(my, s_red[1][w]);
-    }
-    sx = __longlong_as_double(static_cast<long long>(mx));
-    sy = __longlong_as_double(static_cast<long long>(my));
-    dtn = h.next_dt(g, sx, sy);
-    status |= state_status(sx, sy, dtn);
-    __syncthreads();
-    in = out;
-  }
-  if (a.w_last && in != a.w_last) {
-    for (long long c = tid; c < ncell; c += kThreads) {
-      const size_t at = static_cast<size_t>(c / g.nx) * g.ld + c % g.nx;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) a.w_last[v * g.plane + at] = in[v * g.plane + at];
+      for (int w = 1; w < kWaves; ++w) {
+        mx = umax64(mx, s_red[0][w]);
+        my = umax64(my, s_red[1][w]);
+      }
+      atomicMax(&ctl->max_x, mx);
+      atomicMax(&ctl->max_y, my);
+      __threadfence();  // the maxima and the workgroup's cells, then the count
+      const u64 f = __hip_atomic_fetch_add(&ctl->finished, 1ull, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      if (f == (static_cast<u64>(k) + 1) * per_step - 1) {  // the step's last piece
+        const double nx = value(atomicExch(&ctl->max_x, 0ull));
+        const double ny = value(atomicExch(&ctl->max_y, 0ull));
+        const double next = h.next_dt(g, nx, ny);
+        const unsigned int status = state_status(nx, ny, next);
+        if (status) atomicOr(&s->status, status);
+        put(&ctl->sx, bits(nx));
+        put(&ctl->sy, bits(ny));
+        put(&ctl->dt, bits(next));
+        stores_done();
+        put(&ctl->steps, static_cast<u64>(k) + 1);
+      }
     }
   }
   if (tid == 0) {
-    put(&ctl->arrived, 0);
-    put(&ctl->decision, 0);
-    s->cur_sx = sx;
-    s->cur_sy = sy;
-    s->dt = dtn;
-    if (log) s->nstep = log_n + static_cast<unsigned int>(a.nsteps);
-    if (status) atomicOr(&s->status, status);
+    stores_done();
+    const u64 left = __hip_atomic_fetch_add(&ctl->left, 1ull, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+    if (left == gridDim.x - 1) {  // all are done
+      s->cur_sx = value(peek(&ctl->sx));
+      s->cur_sy = value(peek(&ctl->sy));
+      s->dt = value(peek(&ctl->dt));
+      if (log) s->nstep = log_n + static_cast<unsigned int>(a.nsteps);
+      put(&ctl->ticket, 0);
+      put(&ctl->finished, 0);
+      put(&ctl->steps, 0);
+      put(&ctl->left, 0);
+      put(&ctl->arrived, 0);
+      put(&ctl->decision, 0);
+    }
   }
 }
 
@@ -591,11 +656,15 @@ hipError_t launch_run(const Args& a, int model, hipStream_t st) {
     h = general_fn<Spray>(bc);
   }
   if (!f) return hipErrorInvalidValue;
+  // every state of the run by tickets has a buffer, the first another than win
+  if (!a.w_last ? a.every != 1 || a.nsaves < a.nsteps : a.win == state_buffer(a, 1))
+    return hipErrorInvalidValue;
   Args copy = a;
-  void* args[] = {&copy};
+  Pieces pieces = make_pieces(a.g.nx, a.g.ny);
+  void* args[] = {&copy, &pieces};
   const hipError_t e = hipLaunchKernel(f, dim3(a.plan.tiles), dim3(waves(nv) * kWave), args, 0, st);
   if (e != hipSuccess) return e;
-  return hipLaunchKernel(h, dim3(1), dim3(kGeneralThreads), args, 0, st);
+  return hipLaunchKernel(h, dim3(pieces.count), dim3(kGeneralThreads), args, 0, st);
 }
 
 }  // namespace cluster

@@ -57,6 +57,12 @@ struct Control {
   u64 decision;  // 0 open, 1 go (all have started), 2 no go
   u64 done;      // workgroups that have finished the run
   u64 abort;     // a wait ran out of time
+  // of the run by tickets (after "no go"):
+  u64 ticket, finished;  // pieces handed out, pieces done
+  u64 steps;             // steps done
+  u64 left;              // workgroups that have left
+  u64 max_x, max_y;      // speed maxima of the step under way
+  u64 sx, sy, dt;        // of the state after `steps` steps: maxima, next dt
 };
 constexpr int kControlWords = 32;
 
@@ -100,11 +106,27 @@ inline bool make_plan(int nv, int nx, int ny, Plan* p) {
   return true;
 }
 
+// Pieces of a step of a run by tickets: consecutive cells (row-major), a
+// multiple of the workgroup's threads, of at most kMaxTiles workgroups.
+constexpr int kGeneralThreads = 512;
+struct Pieces {
+  long long cells;  // of a piece
+  int count;
+};
+inline Pieces make_pieces(int nx, int ny) {
+  const long long n = static_cast<long long>(nx) * ny;
+  Pieces p;
+  p.cells = (n + kMaxTiles * kGeneralThreads - 1) / (kMaxTiles * kGeneralThreads) * kGeneralThreads;
+  p.count = static_cast<int>((n + p.cells - 1) / p.cells);
+  return p;
+}
+
 struct Args {
   const double* win;          // state 0
-  double* w_last;             // receives state nsteps (may be null)
+  double* w_last;             // receives state nsteps (null: every state is saved)
   double* w_prev;             // receives state nsteps - 1 (may be null)
-  double* spare;              // general path only: a buffer to step through
+  double* spare;              // run by tickets: the states an odd number of steps before
+                              // the last that are not saved (w_prev, where that is given)
   const double* ug;
   GridScratch* scr;
   u64* area;                  // control words, words of the tiles, maxima
@@ -176,10 +198,17 @@ __device__ __forceinline__ double step_dt(const Args& a, int k, double sx, doubl
 }
 
 // Where state k is saved, or null.
-__device__ __forceinline__ double* saved(const Args& a, int k) {
+__host__ __device__ __forceinline__ double* saved(const Args& a, int k) {
   if (a.every <= 0 || k % a.every != 0) return nullptr;
   const int q = k / a.every;
   return q >= 1 && q <= a.nsaves ? a.saves[q - 1] : nullptr;
+}
+
+// Where a run by tickets keeps state k > 0: w_last and spare in turn between
+// the saved ones.
+__host__ __device__ __forceinline__ double* state_buffer(const Args& a, int k) {
+  if (double* const p = saved(a, k)) return p;
+  return (a.nsteps - k) % 2 == 0 ? a.w_last : a.spare;
 }
 
 }  // namespace cluster

@@ -148,3 +148,15 @@ def test_unordered_runs_fit_the_chip_together(calls, sizes):
             for k in list(a):
                 a |= after[k]
         assert 0 < width(after, [r[0] for r in runs]) <= 256
+
+
+@pytest.mark.parametrize("nx,ny,blocks", [(64, 64, 8), (200, 150, 59), (1024, 1024, 256),
+                                          (1054, 1140, 235)])
+def test_a_run_that_cannot_have_the_chip_gets_more_than_one_cu(calls, nx, ny, blocks):
+    (_, log), = calls(("grid", "a", nx, ny), ("run", "a"))[1:]
+    assert [q[0] for q in log] == ["launch", "launch", "record"]
+    (_, tiles, _, _), (_, behind, threads, _) = log[:2]
+    assert tiles <= 256 and threads == 512
+    # pieces of whole rounds of the workgroup's threads cover the cells
+    cells = -(-nx * ny // (256 * 512)) * 512
+    assert behind == blocks == -(-nx * ny // cells)

@@ -230,3 +230,76 @@ def test_a_run_that_broke_off_is_not_built_upon(model, nx, ny):
         da, db = a.run(steps, record_dt=True), b.run(steps, record_dt=True)
         assert torch.equal(da, db)
         same(a, b)
+
+
+def no_go(s):
+    """The workgroups of the next run will not all start: the decision, taken by
+    the host. (Every kernel of the run ends as it does after a real one.)"""
+    torch.cuda.synchronize()
+    control(s)[1] = 2
+
+
+@pytest.mark.parametrize("model", [0, 1, 2])
+@pytest.mark.parametrize("bc", [0, 1, 2])
+def test_runs_that_cannot_have_the_chip(model, bc):
+    """The same states, other buffers, dts, logs, maxima and status as step
+    launches; nothing is left behind for the next run."""
+    for n, (nx, ny) in enumerate([(97, 193), (125, 64), (200, 150), (1, 5200), (1711, 4),
+                                  (700, 701)]):
+        print(f"model {model} bc {bc} {nx}x{ny}", flush=True)
+        (a, b), W = solvers(model, bc, nx, ny, layout=n % 2, pad=n % 3)
+        b.set_tiling(8, 1)  # (no run in one workgroup)
+        for steps in (3, 4, 7):
+            no_go(a)
+            da, db = a.run(steps, record_dt=True), b.run(steps, record_dt=True)
+            assert torch.equal(da, db)
+            same(a, b)
+            oa, ob = (s.wb if s.current_storage() is s.wa else s.wa for s in (a, b))
+            assert torch.equal(oa, ob)
+            assert not control(a)[:10].any()  # (all but the last maxima and dt)
+        dt = 0.3 * b.cfl_dt()[0]
+        for call in (lambda s: s.run_fixed(3, dt), lambda s: s.run_dts([dt, 0.5 * dt, dt]),
+                     lambda s: s.run_fixed(4, 1e3 * dt)):
+            no_go(a)
+            call(a)
+            call(b)
+            assert a.status(clear=True) == b.status(clear=True)
+            assert torch.equal(a.state(), b.state())
+        for s in (a, b):
+            s.run(5)  # on the chip again
+        same(a, b)
+
+
+@pytest.mark.parametrize("nsteps,every", [(1, 1), (7, 1), (8, 3), (9, 3), (10, 4), (66, 1),
+                                          (131, 2)])
+def test_checkpointed_runs_that_cannot_have_the_chip(nsteps, every):
+    (a, b), W = solvers(1, 1, 150, 110, layout=1)
+    got = []
+    for s in (a, b):
+        s.set_state(W)
+        if s is a:
+            no_go(a)
+        ck, dts = s.run_ckpt(nsteps, every)
+        end = s.state()
+        if s is a:
+            no_go(a)
+        lam = s.adjoint(ck, every, dts, torch.ones_like(end))
+        got.append([end, dts, lam.clone()] + [c.clone() for c in ck])
+        assert s.sync() == 0
+    assert all(torch.equal(x, y) for x, y in zip(*got))
+    torch.cuda.synchronize()
+    control(a)[:2] = 0  # (a backward pass that recomputes nothing leaves the decision)
+    for s in (a, b):
+        s.run(3)
+    same(a, b)
+
+
+def test_a_bad_state_that_cannot_have_the_chip():
+    (a, b), W = solvers(1, 1, 130, 90)
+    bad = W.copy()
+    bad[0, 40, 70] = -1.0
+    for s in (a, b):
+        s.set_state(bad)
+        no_go(a)
+        s.run(3)
+        assert s.sync() == _lib.FVM_ENONFINITE
