@@ -355,7 +355,8 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *  - fvm_run, fvm_run_fixed, fvm_run_dts, fvm_run_ckpt and the recomputation
  *    of fvm_adjoint_run on a grid that up to 256 tiles of 62 columns and 300
  *    (advection), 76 (Euler) or 50 (spray) rows cover, e.g. 1024 x 1024 Euler,
- *    run on up to 256 workgroups that exchange their tiles' edges, unless the
+ *    run on up to 256 workgroups that exchange their tiles' edges, unless they
+ *    are of one or two steps (three, where checkpointed or recomputed), the
  *    caller has chosen a strip shape (fvm_set_tiling, fvm_set_cells_per_lane),
  *    the stream is being captured or the stream is another device's than the
  *    grid's or the current one. Such runs on different streams of a process go

@@ -903,6 +903,19 @@ static cluster::Args cluster_args(const fvm_grid* g, int mode, int nsteps, const
   return a;
 }
 
+// The fewest steps for which a run goes on the chip: start, loads and the last two
+// states' stores cost it 10 to 25 us. us a call, steps / chip: one step of 1024^2
+// Euler 28.5 / 47.6, 512^2 21.0 / 31.0, 200 x 150 21.2 / 20.5, of 860 x 900 spray
+// 37.6 / 51.7, of 512^2 advection 21.3 / 26.8; two steps 51.5 / 59.9, 32.4 / 38.1,
+// 22.0 / 25.2, 69.6 / 66.6, 24.1 / 31.8; three 79.6 / 73.4, 50.7 / 45.5, 34.3 / 30.1,
+// 106 / 82.6, 39.7 / 36.9. Of steps that are not launched as a graph
+// (checkpointed runs and their recomputation): 1024^2 with every state saved, two
+// steps 65.2 / 76.4, three 89.4 / 92.5, four 113 / 110, 300^2 three 42.3 / 46.2, four
+// 53.7 / 51.6; one step recomputed 141 / 178 in a backward pass of four, three
+// 315 / 323 in one of eight, eight 401 / 394 in one of nine.
+constexpr int kMinChipRun = 3;
+constexpr int kMinChipSteps = 4;
+
 // One workgroup is the better place for an adaptive run of this grid, or the
 // only one on the chip that is open to it (a captured stream, a strip shape).
 static bool one_workgroup(const fvm_grid* g) {
@@ -928,7 +941,7 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
     g->speeds_valid = true;
     return FVM_OK;
   }
-  if (kind != 2 && nsteps > 0 && cluster_ok(g)) {
+  if (kind != 2 && nsteps >= kMinChipRun && cluster_ok(g)) {
     double* other = g->other(g->cur);
     double* last = nsteps % 2 ? other : g->cur;
     cluster::Args a = cluster_args(
@@ -995,33 +1008,31 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
     rc = dev_err(hipMemcpyAsync(ckpts[0], g->cur, bytes, hipMemcpyDeviceToDevice, g->stream));
     if (rc) return rc;
   }
-  if (nsteps > 0 && cluster_ok(g)) {
+  const double* in = g->cur;
+  int k = 0;
+  if (nsteps >= kMinChipSteps && cluster_ok(g)) {
     // a launch saves so many states at most; the next goes on from the last of
     // them (where a launch cannot have the chip, `last` and the other buffer hold
     // the unsaved states in turn, the current one first: `last` by the parity of
     // the first launch's steps)
     double* last = nullptr;
-    const double* from = g->cur;
-    for (int s = 0;;) {
+    while (nsteps - k >= kMinChipSteps) {
+      const int s = k / ckpt_every;  // state k is checkpoint s
       const int saves = std::min(nck - 1 - s, static_cast<int>(cluster::kMaxSaves));
       const bool end = s + saves == nck - 1;
-      const int steps = end ? nsteps - s * ckpt_every : saves * ckpt_every;
+      const int steps = end ? nsteps - k : saves * ckpt_every;
       if (!last) last = steps % 2 ? g->other(g->cur) : g->cur;
-      cluster::Args a = cluster_args(g, kDtAdaptive, steps, from, last, nullptr);
+      cluster::Args a = cluster_args(g, kDtAdaptive, steps, in, last, nullptr);
       a.every = ckpt_every;
       a.nsaves = saves;
       for (int q = 0; q < saves; ++q) a.saves[q] = ckpts[s + 1 + q];
       rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
       if (rc) return rc;
-      s += saves;
-      if (end) break;
-      from = ckpts[s];
+      k += steps;
+      in = end ? last : ckpts[s + saves];
     }
-    g->cur = last;
-    return FVM_OK;
   }
-  const double* in = g->cur;
-  for (int k = 0; k < nsteps; ++k) {
+  for (; k < nsteps; ++k) {
     double* out;
     if ((k + 1) % ckpt_every == 0 && (k + 1) / ckpt_every < nck)
       out = ckpts[(k + 1) / ckpt_every];
@@ -1455,7 +1466,7 @@ int fvm_adjoint_run(fvm_grid* g, double* const* ckpts, int ckpt_every, const dou
     // recompute W^{k0+1} .. W^{k1-1} into seg_buf[0 .. k1-k0-2]
     const double* in = ckpts[s];
     int k = k0;
-    if (k1 - k0 - 1 > 0 && k1 - k0 - 1 <= cluster::kMaxSaves && cluster_ok(g)) {
+    if (k1 - k0 - 1 >= kMinChipSteps && k1 - k0 - 1 <= cluster::kMaxSaves && cluster_ok(g)) {
       cluster::Args a = cluster_args(g, kDtArray, k1 - k0 - 1, in, nullptr, nullptr);
       a.dts = dts_dev;
       a.k0 = k0;

@@ -32,13 +32,21 @@ def grid(name, nx, ny, stream=0, model=1):
     return code or L.fvm_bind(h, at, at + 4096, None, at + 8192, stream)
 def run(name, steps=20):
     return L.fvm_run_dts(grids[name], steps, 8)
+def buffers(n):
+    return (C.c_void_p * n)(*range(1 << 20, (1 << 20) + 8 * n, 8))
+def ckpt(name, steps, every):
+    n = -(-steps // every)
+    return L.fvm_run_ckpt(grids[name], steps, every, buffers(n), 8)
+def back(name, steps, every):
+    n = -(-steps // every)
+    return L.fvm_adjoint_run(grids[name], buffers(n), every, 8, steps, 1 << 21, 1 << 22, 1 << 23)
 def stream(name, s):
     return L.fvm_set_stream(grids[name], s)
 def device(d):
     return stub.calls_device(d) and 0
 for f, *args in json.loads(sys.argv[2]):
     stub.calls_clear()
-    code = globals()[f](*args) if f in ("grid", "run", "stream", "device") else \\
+    code = globals()[f](*args) if f in ("grid", "run", "ckpt", "back", "stream", "device") else \\
         getattr(L, f)(grids[args[0]], *args[1:])
     log = [q.split() for q in stub.calls_log().decode().splitlines()]
     logs.append([code, [[q[0]] + [int(x) for x in q[1:]] for q in log]])
@@ -160,3 +168,20 @@ def test_a_run_that_cannot_have_the_chip_gets_more_than_one_cu(calls, nx, ny, bl
     # pieces of whole rounds of the workgroup's threads cover the cells
     cells = -(-nx * ny // (256 * 512)) * 512
     assert behind == blocks == -(-nx * ny // cells)
+
+
+def test_short_runs_are_step_launches(calls):
+    """Runs on the chip record their end; a launch for each step, or a graph,
+    where the run is too short to pay for its start."""
+    def on_chip(*actions):
+        return [sum(q[0] == "record" for q in log) for _, log in calls(("grid", "a", 1024, 1024),
+                                                                       *actions)[1:]]
+    for f in ("fvm_run", "fvm_run_fixed"):
+        arg = {"fvm_run": 0, "fvm_run_fixed": 1e-5}[f]
+        assert on_chip(*[(f, "a", n, arg) for n in (1, 2, 3, 4)]) == [0, 0, 1, 1]
+    assert on_chip(*[("run", "a", n) for n in (1, 2, 3, 4)]) == [0, 0, 1, 1]
+    ends = on_chip(*[("ckpt", "a", n, 1) for n in (1, 3, 4, 64, 65, 67, 68)])
+    assert ends == [0, 0, 1, 1, 1, 1, 2]
+    assert on_chip(*[("ckpt", "a", n, 2) for n in (3, 4, 131, 132)]) == [0, 1, 1, 2]
+    # segments of so many steps, the first recomputed from its checkpoint
+    assert on_chip(("back", "a", 8, 2), ("back", "a", 8, 4), ("back", "a", 10, 5)) == [0, 0, 2]
