@@ -917,10 +917,18 @@ constexpr int kMinChipRun = 3;
 constexpr int kMinChipSteps = 4;
 
 // One workgroup is the better place for an adaptive run of this grid, or the
-// only one on the chip that is open to it (a captured stream, a strip shape).
-static bool one_workgroup(const fvm_grid* g) {
-  const long long ncell = static_cast<long long>(g->p.nx) * g->p.ny;
-  return resident_ok(g) && (ncell <= resident_cells(fvm_nvar(g->p.model)) || !cluster_ok(g));
+// only one on the chip that is open to it (a captured stream, a strip shape). Past
+// resident_cells a step takes it longer than several by some 2.6 ns a cell
+// (Euler), but its start takes 6.5 us less: it is the faster one while steps times
+// cells past the limit are below 2500 (us for three and four steps, one / several:
+// Euler 34^2 19.1, 23.7 / 24.3, 28.5, 48^2 29.4, 36.9 / 24.9, 29.0, spray 38^2 20.6, 25.2 /
+// 25.4, 29.7, advection 73^2 21.8, 26.0 / 24.9, 29.0).
+constexpr long long kShortResident = 2500;
+static bool one_workgroup(const fvm_grid* g, int nsteps) {
+  if (!resident_ok(g)) return false;
+  const long long past =
+      static_cast<long long>(g->p.nx) * g->p.ny - resident_cells(fvm_nvar(g->p.model));
+  return past <= 0 || nsteps < kMinChipRun || past * nsteps < kShortResident || !cluster_ok(g);
 }
 
 static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, double* log,
@@ -930,7 +938,7 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
   if ((kind == 0 || kind == 3) && !g->speeds_valid) rc = enqueue_cfl(g, nullptr);
   if (rc == FVM_OK) rc = arm_log(g, log, nsteps);
   if (rc) return rc;
-  if (kind == 0 && nsteps > 0 && one_workgroup(g)) {
+  if (kind == 0 && nsteps > 0 && one_workgroup(g, nsteps)) {
     double* other = g->other(g->cur);
     double* last = nsteps % 2 ? other : g->cur;
     double* prev = nsteps % 2 ? g->cur : other;

@@ -185,3 +185,12 @@ def test_short_runs_are_step_launches(calls):
     assert on_chip(*[("ckpt", "a", n, 2) for n in (3, 4, 131, 132)]) == [0, 1, 1, 2]
     # segments of so many steps, the first recomputed from its checkpoint
     assert on_chip(("back", "a", 8, 2), ("back", "a", 8, 4), ("back", "a", 10, 5)) == [0, 0, 2]
+
+
+def test_short_runs_of_small_grids_stay_in_one_workgroup(calls):
+    for side, steps, one in ((48, 1, True), (48, 2, True), (48, 3, False), (40, 4, True),
+                             (40, 5, False), (34, 18, True), (34, 19, False)):
+        _, _, (_, log) = calls(("grid", "a", side, side), ("fvm_run", "a", 1, 0),
+                               ("fvm_run", "a", steps, 0))
+        assert ([q[:2] for q in log] == [["launch", 1]]) == one
+        assert (log[-1][0] == "record") != one

@@ -244,7 +244,7 @@ def no_go(s):
 def test_runs_that_cannot_have_the_chip(model, bc):
     """The same states, other buffers, dts, logs, maxima and status as step
     launches; nothing is left behind for the next run."""
-    for n, (nx, ny) in enumerate([(97, 193), (125, 64), (200, 150), (1, 5200), (1711, 4),
+    for n, (nx, ny) in enumerate([(97, 193), (125, 64), (200, 150), (1, 6100), (1711, 4),
                                   (700, 701)]):
         print(f"model {model} bc {bc} {nx}x{ny}", flush=True)
         (a, b), W = solvers(model, bc, nx, ny, layout=n % 2, pad=n % 3)
