@@ -340,7 +340,8 @@ int fvm_set_adjoint_tiling(fvm_grid* g, int rows_per_strip, int waves_per_block,
 /* Lanes of the fused step: 1 = one cell per lane (any pitch), 2 = two
  * adjacent cells per lane with 16-byte accesses (needs an even ld and 16-byte
  * aligned buffers; otherwise the call falls back to 1), 0 = the model's
- * default. Results are bitwise identical either way.
+ * default (and takes an earlier choice back, also for fvm_set_resident_runs).
+ * Results are bitwise identical either way.
  * fvm_get_cells_per_lane returns the value in use. */
 int fvm_set_cells_per_lane(fvm_grid* g, int cells_per_lane);
 int fvm_get_cells_per_lane(const fvm_grid* g);

@@ -358,7 +358,8 @@ struct fvm_grid {
   cluster::Plan plan{};  // .. their tiles, and whether there are any
   bool plan_ok = false;
   bool default_strips = true;  // rows and wpb are the default for the layout
-  bool strips_asked = false;  // the caller chose a strip shape: its runs are step launches
+  // the caller has chosen a strip shape or lane layout: its runs are step launches
+  bool strips_asked = false, lanes_asked = false;
   int device = -1;       // current at bind, -1 if it cannot hold the plan's tiles at once
   int cus = 0;           // .. its CUs
   int cpl = 1;       // layout in use
@@ -872,7 +873,8 @@ static bool resident_ok(const fvm_grid* g) {
 // grid's device, which is the current one (the turns' events are its own), and
 // is not being captured (the launch may have to wait for another stream's).
 static bool cluster_ok(const fvm_grid* g) {
-  if (!g->resident || !g->plan_ok || g->device < 0 || g->strips_asked || g->halo.s || g->halo.n)
+  if (!g->resident || !g->plan_ok || g->device < 0 || g->strips_asked || g->lanes_asked ||
+      g->halo.s || g->halo.n)
     return false;
   int dev = -1, sdev = -1;
   if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(g->stream, &sdev) != hipSuccess ||
@@ -1350,7 +1352,7 @@ int fvm_autotune(fvm_grid* g, const char* cache_path) {
 
 int fvm_set_cells_per_lane(fvm_grid* g, int cpl) {
   if (!g || cpl < 0 || cpl > 2) return FVM_EINVAL;
-  g->strips_asked = g->strips_asked || cpl != 0;
+  g->lanes_asked = cpl != 0;
   g->cpl_req = cpl;
   choose_layout(g);
   return FVM_OK;

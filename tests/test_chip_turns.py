@@ -194,3 +194,16 @@ def test_short_runs_of_small_grids_stay_in_one_workgroup(calls):
                                ("fvm_run", "a", steps, 0))
         assert ([q[:2] for q in log] == [["launch", 1]]) == one
         assert (log[-1][0] == "record") != one
+
+
+def test_a_lane_layout_can_be_taken_back(calls):
+    def chip(*actions):
+        return [log[-1][0] == "record" for (_, log), (f, *_) in
+                zip(calls(("grid", "a", 300, 200), *actions)[1:], actions) if f == "run"]
+    lanes = lambda n: ("fvm_set_cells_per_lane", "a", n)
+    run = ("run", "a")
+    assert chip(run, lanes(1), run, lanes(0), run, lanes(2), lanes(0), run) == [1, 0, 1, 1]
+    # a strip shape has no default to go back to; 0 keeps it
+    assert chip(("fvm_set_tiling", "a", 8, 2), run, ("fvm_set_tiling", "a", 0, 0), lanes(0),
+                run) == [0, 0]
+    assert chip(("fvm_set_tiling", "a", 0, 0), run) == [1]
