@@ -60,19 +60,6 @@ constexpr Node kNodes[] = {
     {0.413779204371605, 0.07061164739128678}, {0.3419940908257585, 0.07288658239580406},
     {0.2681521850072537, 0.07472316905796826}, {0.1926975807013711, 0.07611036190062624},
     {0.11608407067525521, 0.07703981816424797}, {0.03877241750605082, 0.0775059479784248},
-    // 48 points
-    {0.9987710072524261, 0.0031533460523058385}, {0.9935301722663508, 0.0073275539012762625},
-    {0.9841245837228269, 0.01147723457923454}, {0.9705915925462473, 0.015579315722943849},
-    {0.9529877031604309, 0.01961616045735553}, {0.9313866907065543, 0.02357076083932438},
-    {0.9058791367155696, 0.027426509708356948}, {0.8765720202742479, 0.03116722783279809},
-    {0.8435882616243935, 0.03477722256477044}, {0.8070662040294426, 0.03824135106583071},
-    {0.7671590325157404, 0.04154508294346475}, {0.7240341309238146, 0.04467456085669428},
-    {0.6778723796326639, 0.04761665849249048}, {0.6288673967765136, 0.05035903555385447},
-    {0.5772247260839727, 0.05289018948519367}, {0.523160974722233, 0.055199503699984165},
-    {0.4669029047509584, 0.057277292100403214}, {0.4086864819907167, 0.059114839698395635},
-    {0.34875588629216075, 0.06070443916589388}, {0.28736248735545555, 0.062039423159892665},
-    {0.22476379039468905, 0.06311419228625402}, {0.1612223560688917, 0.06392423858464819},
-    {0.0970046992094627, 0.06446616443595009}, {0.03238017096286936, 0.06473769681268392},
     // 64 points
     {0.9993050417357722, 0.001783280721696433}, {0.9963401167719553, 0.004147033260562468},
     {0.9910133714767443, 0.006504457968978363}, {0.983336253884626, 0.008846759826363947},
@@ -146,15 +133,18 @@ struct Rule {
 // 0.008..1, skewed, and the lognormal ones of the spray workload) the
 // smallest curvature within three standard deviations of the mean at which a
 // rule is more than 1e-12 off, and further off than 16 panels of 8 points,
-// was 316, 515, 1172, 2510 and 4283: the lines lie below those.
+// was 316, 1172, 2510 and 4283: the lines lie below those.
 constexpr Rule kRules[] = {
-    {0, 20, 250.0}, {20, 24, 400.0}, {44, 32, 1000.0}, {76, 40, 2000.0}, {116, 48, 3500.0}};
-constexpr int kRuleCount = 5;
+    {0, 20, 250.0}, {20, 32, 1000.0}, {52, 40, 2000.0}, {92, 48, 3500.0}};
+constexpr int kRuleCount = 4;
+
+constexpr int kPairs = kRules[kRuleCount - 1].first + kRules[kRuleCount - 1].pairs;
+static_assert(kPairs == sizeof kNodes / sizeof kNodes[0], "nodes of all rules");
 
 struct Table {
-  double v[164 * kStride];
+  double v[kPairs * kStride];
   constexpr Table() : v() {
-    for (int q = 0; q < 164; ++q) {
+    for (int q = 0; q < kPairs; ++q) {
       v[q * kStride] = kNodes[q].t;
       // P_j = 2 int t^j e^p dx, dx = dt / 2: the rule's weight times t^j
       double c = kNodes[q].w;
@@ -250,6 +240,18 @@ __device__ __forceinline__ void moments(const double* c, int rule, double* P) {
 #pragma unroll
     for (int j = 0; j < kStride; ++j) row[j] = next[j];
   }
+}
+
+// The same by the cell's own rule: the rules that cells of the wave want, one
+// after the other, each for its cells, so that a cell's moments do not depend on
+// its neighbours in the wave. 1024^2 cells of the spray workload, ten steps: 2114 us
+// with one rule for the wave, the finest any cell wants; 2191 so, and 2406 with a
+// further rule of 48 points, which a third of the waves would want beside the 64.
+__device__ __forceinline__ void moments_by(bool live, int rule, const double* c, double* P) {
+#pragma unroll
+  for (int j = 0; j < kMoments; ++j) P[j] = 0.0;
+  for (int r = 0; r < kRuleCount; ++r)
+    if (live && rule == r) moments(c, __builtin_amdgcn_readfirstlane(rule), P);
 }
 
 // The four weighted moments and the Hankel matrix they span, factored as
@@ -371,14 +373,10 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
     const int full = rule_of(curv);
     // the coarse rule resolves what a steep cell needs to about 1e-6 up to
     // a curvature of 1000; steeper ones use finer rules from the start
-    int want = coarse ? (full <= 2 ? 0 : full - 1) : full;
+    int want = coarse ? (full <= 1 ? 0 : full - 1) : full;
     want = want < kRuleCount ? want : kRuleCount - 1;
-    want = run ? want : 0;
-    int rule = 0;
-#pragma unroll
-    for (int k = 1; k < kRuleCount; ++k) rule = __any(want >= k) ? k : rule;
     double P[kMoments], N[kMoments - 1];
-    moments(c, rule, P);
+    moments_by(run, want, c, P);
 #pragma unroll
     for (int k = 0; k + 1 < kMoments; ++k) N[k] = 0.5 * (P[k] + P[k + 1]);
     // d1 = H^{-1} g: the Newton step; lam2 = g.d1 for unit mass
@@ -395,7 +393,7 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
       phi = logd(H.ok ? N[0] : 1.0) -
             kLn2 * fma(c[1], tau1, fma(c[2], tau2, fma(c[3], tau3, c[0])));
     const bool reject = !good || (have && !(lam2 < 1e-6) && !(phi <= phi_last));
-    const bool accept = run && !reject && lam2 <= 1e-10 && rule >= full;
+    const bool accept = run && !reject && lam2 <= 1e-10 && want >= full;
     // second order: H d2 = -1/2 sum_ij d_i d_j N_{k+i+j}
     double q[7] = {d[0] * d[0],
                    2.0 * d[0] * d[1],

@@ -345,19 +345,15 @@ __global__ __launch_bounds__(kMeThreads, 2) void maxent_adjoint_source_kernel(Ad
       double l[4] = {0.0, 0.0, 0.0, 0.0}, mmh, n0;
       entropy::Result e;
       bool ok = wave_closure(live, ws, r, false, l, mmh, n0, e);
-      // the moments at the converged multipliers, by the finest rule any lane
-      // needs
+      // the moments at the converged multipliers
       const bool quick = live && e.ok;
       if (__any(quick)) {
         double P[entropy::kMoments], N[7];
         double c[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) c[k] = quick ? e.c[k] : 0.0;
-        int rule = 0;
-        const int want = quick ? entropy::rule_of(entropy::curvature(c, -1.0, 1.0)) : 0;
-#pragma unroll
-        for (int k = 1; k < entropy::kRuleCount; ++k) rule = __any(want >= k) ? k : rule;
-        entropy::moments(c, rule, P);
+        const int want = entropy::rule_of(entropy::curvature(c, -1.0, 1.0));
+        entropy::moments_by(quick, min(want, entropy::kRuleCount - 1), c, P);
 #pragma unroll
         for (int k = 0; k < 7; ++k) N[k] = 0.5 * (P[k] + P[k + 1]);
         const entropy::Hankel H(N);
