@@ -515,18 +515,23 @@ class FVRun(torch.autograd.Function):
     discrete adjoint with the forward dts held fixed, recomputing each
     segment of `every` steps from its checkpoint.
 
-    FVRun.apply(W0, solver, nsteps, every) with W0 of shape (nVar, Ny, Nx).
+    FVRun.apply(W0, solver, nsteps, every) with W0 of shape (nVar, Ny, Nx);
+    every None: as often as memory allows (_ckpt_every).
     """
 
     @staticmethod
-    def forward(ctx, W0, solver: Solver, nsteps: int, every: int):
+    def forward(ctx, W0, solver: Solver, nsteps: int, every: int | None):
         solver.set_state(W0.detach())
-        nck = (nsteps + every - 1) // every
-        try:  # one allocation, not one a state
-            ck = torch.empty((nck,) + tuple(solver.wa.shape), dtype=torch.float64,
-                             device=solver.device).unbind(0)
-        except torch.cuda.OutOfMemoryError:  # not in one piece
-            ck = [torch.empty_like(solver.wa) for _ in range(nck)]
+        ck = None
+        if every is None:
+            every, few = _ckpt_every(solver, nsteps), _few_ckpts(nsteps)
+            if every < few:
+                try:
+                    ck = _ckpt_buffers(solver, nsteps, every, True)
+                except torch.cuda.OutOfMemoryError:  # a limit of this process's own
+                    every = few
+        if ck is None:
+            ck = _ckpt_buffers(solver, nsteps, every)
         ck, dts = solver._run_ckpt(nsteps, every, ck)
         ctx.solver = solver
         ctx.every = every
@@ -541,6 +546,27 @@ class FVRun(torch.autograd.Function):
         return lam[:, :, :s.p.nx].clone(memory_format=torch.contiguous_format), None, None, None
 
 
+def _few_ckpts(nsteps: int) -> int:
+    """Steps between checkpoints that keep the fewest states, about
+    2 sqrt(nsteps)."""
+    return max(1, int(round(math.sqrt(nsteps))))
+
+
+def _ckpt_buffers(solver: Solver, nsteps: int, every: int, backward: bool = False):
+    """Storage for the checkpoints of a run; backward: only if the backward
+    pass's buffers fit beside it."""
+    nck = (nsteps + every - 1) // every
+    shape = tuple(solver.wa.shape)
+    try:  # one allocation, not one a state
+        ck = torch.empty((nck,) + shape, dtype=torch.float64, device=solver.device).unbind(0)
+    except torch.cuda.OutOfMemoryError:  # not in one piece
+        ck = [torch.empty_like(solver.wa) for _ in range(nck)]
+    if backward and 8 * solver.wa.numel() * nck > solver.memory // 10000:
+        # (a segment, the result and two multiplier fields; freed at once)
+        torch.empty((every + 3,) + shape, dtype=torch.float64, device=solver.device)
+    return ck
+
+
 def _ckpt_every(solver: Solver, nsteps: int) -> int:
     """Steps between two checkpoints of a differentiable run. sqrt(nsteps) keeps
     the fewest states, about 2 sqrt(nsteps), and computes nearly every step
@@ -550,7 +576,7 @@ def _ckpt_every(solver: Solver, nsteps: int) -> int:
     run of less than a ten thousandth does not): 50 steps of
     1024^2 Euler and their gradient, every state kept (1.7 GB of 288), take 2256 us
     instead of 3000, 16 steps of 512^2 spray 549 instead of 746."""
-    every = max(1, int(round(math.sqrt(nsteps))))
+    every = _few_ckpts(nsteps)
     memory, state = solver.memory, 8 * solver.wa.numel()
     for e in range(1, every):
         states = state * (-(-nsteps // e) + e)
@@ -566,5 +592,4 @@ def _ckpt_every(solver: Solver, nsteps: int) -> int:
 def fvrun(W0: torch.Tensor, solver: Solver, nsteps: int, every: int | None = None):
     """W^nsteps from W^0, differentiable. every: steps between the states kept
     for the backward pass, which computes the ones between again."""
-    every = every or _ckpt_every(solver, nsteps)
-    return FVRun.apply(W0, solver, nsteps, every)
+    return FVRun.apply(W0, solver, nsteps, every or None)

@@ -138,6 +138,27 @@ def test_the_default_checkpoints_change_no_gradient(nsteps):
     assert torch.equal(*grads)
 
 
+def test_gradients_under_a_memory_limit():
+    """A process that may use so little memory that every state does not fit, but
+    few checkpoints do: they are what it gets."""
+    (a, b), W = solvers(1, 1, 700, 700)
+    X = torch.from_numpy(W).cuda().requires_grad_(True)
+    state = a.wa.numel() * 8
+    (fvrun(X, b, 50, 7) ** 2).sum().backward()
+    want = X.grad.clone()
+    X.grad = None
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    have = torch.cuda.memory_reserved() + 32 * state  # (8 + 7 states and some)
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(have / total)
+    try:
+        (fvrun(X, a, 50) ** 2).sum().backward()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(X.grad, want)
+
+
 @pytest.mark.parametrize("model,every", [(1, 1), (1, 4), (2, 3), (0, 5)])
 def test_checkpointed_runs_and_gradients(model, every):
     (a, b), W = solvers(model, 0 if model == 2 else 1, 150, 110, layout=1)
