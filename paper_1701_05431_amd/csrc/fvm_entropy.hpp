@@ -243,10 +243,7 @@ __device__ __forceinline__ void moments(const double* c, int rule, double* P) {
 }
 
 // The same by the cell's own rule: the rules that cells of the wave want, one
-// after the other, each for its cells, so that a cell's moments do not depend on
-// its neighbours in the wave. 1024^2 cells of the spray workload, ten steps: 2114 us
-// with one rule for the wave, the finest any cell wants; 2191 so, and 2406 with a
-// further rule of 48 points, which a third of the waves would want beside the 64.
+// after the other, each for its cells.
 __device__ __forceinline__ void moments_by(bool live, int rule, const double* c, double* P) {
 #pragma unroll
   for (int j = 0; j < kMoments; ++j) P[j] = 0.0;
@@ -318,6 +315,15 @@ struct Result {
 // |skewness| below 2, and p no steeper than the finest rule allows; the
 // others, and any that does not converge in kMaxEvals evaluations, return
 // ok = false.
+//
+// A cell's evaluations are its own, whatever the other cells of the wave: each
+// is made by the rule the cell wants, and the wave takes one rule at a time, the
+// coarsest any cell wants, while cells that want a finer one wait. us for ten
+// steps of the spray workload, with the finest rule any cell wants for all cells /
+// so: 1024^2 from kept multipliers 2123 / 2148, cold 2952 / 3027, 100^2 400 / 412 and
+// 613 / 642. (With each evaluation made by every rule that is wanted 2191 at 1024^2,
+// and 2406 with a further rule of 48 points, which a third of the waves want beside
+// the 64.)
 constexpr int kMaxEvals = 24;
 
 __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, const double* c_in) {
@@ -367,16 +373,20 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
   bool cold_left = start;          // the cold start has not been tried yet
   bool coarse = true, have = false;
   double phi_last = 0.0, shrink = 1.0;
-  for (int it = 0; it < kMaxEvals; ++it) {
-    if (!__any(run)) break;
+  int evals = 0;
+  while (__any(run)) {
     const double curv = curvature(c, t_lo, t_hi);
     const int full = rule_of(curv);
     // the coarse rule resolves what a steep cell needs to about 1e-6 up to
     // a curvature of 1000; steeper ones use finer rules from the start
     int want = coarse ? (full <= 1 ? 0 : full - 1) : full;
     want = want < kRuleCount ? want : kRuleCount - 1;
+    int rule = kRuleCount - 1;
+#pragma unroll
+    for (int k = kRuleCount - 2; k >= 0; --k) rule = __any(run && want == k) ? k : rule;
+    const bool turn = run && want == rule;
     double P[kMoments], N[kMoments - 1];
-    moments_by(run, want, c, P);
+    moments(c, rule, P);
 #pragma unroll
     for (int k = 0; k + 1 < kMoments; ++k) N[k] = 0.5 * (P[k] + P[k + 1]);
     // d1 = H^{-1} g: the Newton step; lam2 = g.d1 for unit mass
@@ -389,11 +399,11 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
     const bool good = H.ok && lam2 >= 0.0 && finite(lam2);
     // the dual's value, where a step may have gone too far
     double phi = 0.0;
-    if (__any(run && !(lam2 < 1e-6)))
+    if (__any(turn && !(lam2 < 1e-6)))
       phi = logd(H.ok ? N[0] : 1.0) -
             kLn2 * fma(c[1], tau1, fma(c[2], tau2, fma(c[3], tau3, c[0])));
     const bool reject = !good || (have && !(lam2 < 1e-6) && !(phi <= phi_last));
-    const bool accept = run && !reject && lam2 <= 1e-10 && want >= full;
+    const bool accept = turn && !reject && lam2 <= 1e-10 && want >= full;
     // second order: H d2 = -1/2 sum_ij d_i d_j N_{k+i+j}
     double q[7] = {d[0] * d[0],
                    2.0 * d[0] * d[1],
@@ -417,7 +427,7 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
     const double lam22 = fma(h[0], d2[0], fma(h[1], d2[1], fma(h[2], d2[2], h[3] * d2[3]))) * H.r0;
     const bool whole = 4.0 * lam22 <= lam2;
     const double f = whole || !good ? 1.0 : 0.5 * root(lam2 * recip(lam22));
-    if (run && full >= kRuleCount && lam2 < 1e-6) {
+    if (turn && full >= kRuleCount && lam2 < 1e-6) {
       run = false;  // at its solution, and steeper than the rules resolve
     } else if (accept) {
       // the last step by the expansion: its third-order terms are lam^3 ~ 1e-15
@@ -435,7 +445,7 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
       c[0] = fma(kLog2e, logd(scale), c[0]);
       r.ok = finite(r.mmh) && finite(r.n0);
       run = false;
-    } else if (run && !reject) {
+    } else if (turn && !reject) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         step[k] = kLog2e * f * fma(f, d2[k], d[k]);
@@ -445,7 +455,7 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
       phi_last = phi;
       have = !(lam2 < 1e-6);  // the next evaluation has a value to compare with
       shrink = 1.0;
-    } else if (run) {
+    } else if (turn) {
       // too far: back to a quarter of the last step, or to the cold start
       shrink *= 0.25;
       if (have && shrink > 1e-4) {
@@ -464,6 +474,7 @@ __device__ __forceinline__ Result solve(bool live, const double* w, bool warm, c
         run = false;
       }
     }
+    if (turn && ++evals == kMaxEvals) run = false;
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k) r.c[k] = c[k];
