@@ -13,7 +13,7 @@ inputs already resident in HBM. The line also carries:
                   the launch stream;
   cpu_baseline -- the CPU oracle on the host cores on a bounded sample;
   workloads    -- the other workloads: spray 2048^2, 256 batched grids
-                  (persistent launch vs one launch per grid), the adjoint at
+                  (one launch a step vs one launch per grid), the adjoint at
                   1024^2 (backward / forward cost) and advection 64^2.
 """
 from __future__ import annotations
@@ -283,6 +283,8 @@ def bench_batch(steps, warmup, layout="rows", tuning=TUNING):
     out = {"workload": inputs.BATCH_256.name, "grids": len(sizes), "cells": cells,
            "pitch": "nx rounded up to a multiple of 16 doubles",
            "steps": steps}
+    # "persistent": one launch a step for all grids, in the schedule the tuner
+    # picks (workgroups that stay, or one per work item)
     for name, per_grid in (("persistent", False), ("per_grid", True)):
         b = Batch(plist)
         b.set_states(states)

@@ -350,9 +350,11 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  * whole run, in one launch, instead of one launch per step (Sec. 2.2.1
  * eq. VF_scheme and eq. CFL_cond; no halo rows; the spray with the lognormal
  * closure only):
- *  - fvm_run on a grid whose two states fit in one workgroup's LDS
- *    (2 x nVar x nx x ny <= 18432 doubles, e.g. advection up to 96 x 96, Euler
- *    up to 48 x 48) runs in one workgroup;
+ *  - fvm_run on a grid of up to 5120 cells (advection) or 1024 (Euler, spray)
+ *    runs in one workgroup; up to what one workgroup's LDS holds
+ *    (2 x nVar x nx x ny <= 18432 doubles: advection 96 x 96, Euler 48 x 48) so do
+ *    runs of one or two steps, runs of nsteps < 2500 / (cells past that limit),
+ *    and those that the next item's conditions keep off the chip;
  *  - fvm_run, fvm_run_fixed, fvm_run_dts, fvm_run_ckpt and the recomputation
  *    of fvm_adjoint_run on a grid that up to 256 tiles of 62 columns and 300
  *    (advection), 76 (Euler) or 50 (spray) rows cover, e.g. 1024 x 1024 Euler,
@@ -403,9 +405,8 @@ int fvm_autotune_adjoint(fvm_grid* g, const double* w, const double* lam_in, dou
 
 /* ---- batches of independent grids -------------------------------------- */
 
-/* Creates a plan for n independent grids solved together, one persistent
- * launch per time step for all of them (each grid keeps its own adaptive
- * dt). p[k] are the grids' parameters (all the same model and boundary
+/* Creates a plan for n independent grids solved together, one launch per
+ * time step for all of them (each grid keeps its own adaptive dt). p[k] are the grids' parameters (all the same model and boundary
  * condition, not spray, not Dirichlet);
  * offsets[k] is the element offset of grid k's state inside the packed
  * buffers, a multiple of 32 elements (256 bytes). */
@@ -438,7 +439,7 @@ int fvm_batch_load(fvm_batch* b, const double* const* src, void* stream);
 int fvm_batch_run(fvm_batch* b, int nsteps, double* dts_dev);
 
 /* The same steps with one launch per grid per step (the reference schedule
- * the persistent launch is compared against). */
+ * the batch's own is compared against). */
 int fvm_batch_run_per_grid(fvm_batch* b, int nsteps, double* dts_dev);
 
 /* Device pointer of the packed buffer holding the current states. */

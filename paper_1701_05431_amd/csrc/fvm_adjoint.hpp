@@ -35,7 +35,9 @@
 // Rows of (W, lambda) loads in flight per adjoint strip beyond the next row, one
 // cell per lane (Euler; advection: kRowsAhead) and two. None for Euler: the
 // second wave of the SIMD covers the loads as well, and a tile is computed in
-// turns of two rows instead of four (1024^2 22.9 -> 20.3 us, 300^2 7.1 -> 5.8).
+// turns of two rows instead of four (alternating: 1024^2 22.9 -> 20.3 us, 300^2 7.1
+// -> 5.8; now 20.9 and 6.4 one launch after the other on the same state, and 22.5 at
+// 1024^2 in a run's backward pass, whose states come from memory).
 #ifndef FVM_ADJ_PREFETCH
 #define FVM_ADJ_PREFETCH 0
 #endif

@@ -29,7 +29,7 @@
 //    Newton iteration with a final check takes five (7 and 13 cold);
 //  - while a cell is far from its solution the coarse 40-point rule is used.
 // Source pass over 1024^2 cells of the spray workload: from kept multipliers
-// 0.90 -> 0.20 ms, cold 2.5 -> 0.29 ms (3,700 and 6,080 vector instructions per 64
+// 0.90 -> 0.19 ms, cold 2.5 -> 0.33 ms (3,640 and 6,570 vector instructions per 64
 // cells; 60 us of the pass are its loads, stores and the reduction).
 #pragma once
 

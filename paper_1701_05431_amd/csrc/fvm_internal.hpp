@@ -143,8 +143,9 @@ struct CflArgs {
 // The speed pass over one grid: workgroups of eight waves, each wave with
 // eight pieces of 64 cells on average, at most one workgroup per CU, because the
 // atomics at their end queue up on one line, 12 ns each (2048 workgroups took
-// 76 us over 1024^2 Euler cells and 179 us over 4096^2; this takes 15 and 93, the
-// latter 5.8 TB/s).
+// 76 us over 1024^2 Euler cells and 179 us over 4096^2, one pass after the other;
+// this takes 15 and 94, the latter 5.7 TB/s; 114 to 117 us, 4.7 TB/s, right behind
+// the launch that wrote the 4096^2 state).
 constexpr int kCflWaves = 8;
 inline int cfl_blocks(const GridGeom& g) {
   const long long pieces = static_cast<long long>((g.nx + kWave - 1) / kWave) * g.ny;

@@ -1,5 +1,5 @@
 // fvm_step.hpp -- device building blocks of the fused step, shared by the
-// single-grid kernel and the persistent batched kernel: boundary index maps,
+// single-grid kernel and the batched kernel: boundary index maps,
 // the marching wave strip, the NaN-propagating speed reduction and the
 // device-side time step.
 #pragma once
@@ -542,9 +542,10 @@ __device__ __forceinline__ bool block_commit(unsigned long long bx, unsigned lon
 
 // Folds the speeds of a grid's cells into (bx, by), this workgroup's share of
 // `blocks` (workgroups of WPB waves); w: variable planes `plane` apart, rows
-// `ld`. COPY: the cells go to `out` (the grid's own plane and ld) on the way. A wave takes pieces of 64 consecutive
-// cells of a row, four pieces at a time so that their loads are in flight
-// together; the pieces are numbered row by row and dealt round-robin.
+// `ld`. COPY: the cells go to `out` (the grid's own plane and ld) on the way. A
+// wave takes pieces of 64 consecutive cells of a row, four pieces at a time so
+// that their loads are in flight together; the pieces are numbered row by row
+// and dealt round-robin.
 template <int WPB, bool COPY, class M>
 __device__ __forceinline__ void row_speeds(const M& m, const double* __restrict__ w, size_t plane,
                                            size_t ld, double* __restrict__ out, const GridGeom& g,

@@ -302,8 +302,8 @@ class Solver:
         return int(lib().fvm_get_cells_per_lane(self.h))
 
     def set_resident_runs(self, enable: bool = True) -> None:
-        """Whole adaptive runs of a grid that fits in one workgroup's LDS in
-        one launch (the default), or one launch per step."""
+        """Runs of a grid that fits on the chip (in one workgroup's LDS, or in
+        that of up to 256) in one launch, the default, or one launch per step."""
         check(lib().fvm_set_resident_runs(self.h, int(bool(enable))), "fvm_set_resident_runs")
 
     def autotune(self, cache_path: str | None = None):
@@ -429,7 +429,8 @@ class Batch:
 
     def set_schedule(self, persistent: bool = True, fit_blocks: bool = False) -> None:
         """Persistent workgroups over a work queue, or one workgroup per item;
-        fit_blocks: row blocks sized so that strips fill whole workgroups."""
+        fit_blocks: row blocks sized so that strips fill whole workgroups. A new
+        batch runs (False, True), not this call's default arguments."""
         check(lib().fvm_batch_set_schedule(self.h, int(bool(persistent)), int(bool(fit_blocks))),
               "fvm_batch_set_schedule")
 
