@@ -365,7 +365,7 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *    grid's or the current one. Such runs on different streams of a process go
  *    on side by side where they fit the chip together, counted in eighths of it
  *    (32 tiles); otherwise a run waits for the earlier ones. Should the
- *    workgroups not all become resident within 2 ms (another process's kernels,
+ *    workgroups not all become resident within 20 ms (another process's kernels,
  *    or long ones of another stream of this process, hold some of the CUs), the
  *    run goes through device memory with as many workgroups as find room, at
  *    some 20 to 80 us a step.

@@ -27,10 +27,12 @@ namespace cluster {
 
 namespace {
 
-// 2 ms of the 100 MHz clock: the workgroups of a run start within some 10 us of
-// each other, or when the kernel that fills the chip has ended (200 us for steps of
-// 4096^2 on another stream); a run by tickets costs 50 us a step more.
-constexpr long long kStartLimit = 200000;
+// 20 ms of the 100 MHz clock. The workgroups of a run start within some 10 us of
+// each other, or when the kernel that fills the chip has ended, and waiting for
+// that is better than sharing the chip with it: 50 steps of 1024^2 beside products
+// of 15 ms each on another stream take 19 ms, by tickets after 2 ms of waiting 87
+// (as step launches 31).
+constexpr long long kStartLimit = 2000000;
 constexpr long long kWaitLimit = 400000000;   // 4 s
 
 // Words other workgroups write or read while the kernel runs: device-scope

@@ -6,6 +6,8 @@ column or row more than a tile, narrower last tiles, fewer rows than waves,
 several tiles in each direction, the largest grids that fit and the first that
 do not; adaptive, fixed and given dts, checkpointed runs and their backward
 pass, runs in a row, and two grids on two streams."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -209,6 +211,33 @@ def test_small_and_large_grids_on_many_streams():
     for a, b in pairs:
         b.run(sum(3 + k for k in range(6)))
         same(a, b)
+
+
+def test_threads_on_streams_of_one_handle():
+    """hipStreamPerThread: one handle, a stream a thread."""
+    (a, _), W = solvers(1, 1, 300, 200)
+    W = torch.from_numpy(W).cuda()
+    a.run(20)
+    want = a.state()
+    torch.cuda.synchronize()
+    got = []
+
+    def work():
+        torch.cuda.set_device(0)
+        (s, _), _ = solvers(1, 1, 300, 200)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.ExternalStream(2)):
+            for _ in range(10):
+                s.set_state(W)
+                s.run(20)
+            got.append((s.sync(), torch.equal(s.state(), want)))
+
+    threads = [threading.Thread(target=work) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == [(0, True)] * 4
 
 
 def test_a_chosen_strip_shape_still_runs_strips():
