@@ -364,11 +364,12 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *    the stream is being captured or the stream is another device's than the
  *    grid's or the current one. Such runs on different streams of a process go
  *    on side by side where they fit the chip together, counted in eighths of it
- *    (32 tiles); otherwise a run waits for the earlier ones. Should the
- *    workgroups not all become resident within 20 ms (another process's kernels,
- *    or long ones of another stream of this process, hold some of the CUs), the
- *    run goes through device memory with as many workgroups as find room, at
- *    some 20 to 80 us a step.
+ *    (32 tiles); a run that finds too little of it free of other streams' runs
+ *    makes its steps in launches and waits for none. Should the workgroups not
+ *    all become resident within 20 ms (another process's kernels, or long ones of
+ *    another stream of this process, hold some of the CUs), the run goes through
+ *    device memory with as many workgroups as find room, at some 20 to 80 us a
+ *    step.
  * States, dts, the dt log, the maxima and the status are bitwise those of
  * the step launches; the other ping-pong buffer ends up holding the state
  * before the last step, as with step launches (fvm_run, fvm_run_fixed,

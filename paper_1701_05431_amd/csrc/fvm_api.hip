@@ -255,66 +255,107 @@ size_t cluster_bytes(const fvm_params& p) {
 
 // Two such runs at once, from two streams, could each hold some of the CUs
 // and wait for the rest, so unordered runs have to fit the chip together. The
-// chip is handed out in parts of 32 CUs: a run takes as many parts as its tiles
-// fill and waits for the runs that had them before; runs of small grids on other
-// streams go on beside it (us for a run(50) on each of 8 streams, in parts / one
-// run at a time / as step launches: Euler 64^2 532 / 2010 / 1148, 200 x 150 1140 /
-// 2178 / 1383, spray 200^2 1330 / 2429 / 1969). A stream is given the parts it had
-// before, then the ones not used for longest. That is no more than a choice: the
-// wait is made also where the handles of two streams are equal
-// (hipStreamPerThread names a stream per thread, and a destroyed stream's handle
-// may be another's by now). One event per part and device, kept until the
-// process ends.
+// chip is handed out in parts of 32 CUs, as many to a run as its tiles fill, and
+// a run takes parts that its own stream had before or whose last run is over;
+// where those do not suffice it does not wait for the other streams (which may
+// have any amount of work ahead of their run) but makes its steps in launches,
+// hipErrorNotReady here. A stream's own parts are waited for, which costs nothing
+// on one stream: equal handles need not be one stream (hipStreamPerThread names a
+// stream per thread, and a destroyed stream's handle may be another's by now). us
+// for a run(50) on each of 8 streams, so / one run at a time / all as step launches:
+// Euler 64^2 540 / 2010 / 1148, 200 x 150 1074 / 2178 / 1383, spray 200^2 1272 / 2429 /
+// 1969; 512^2, which fills the chip, on 4 streams 1225 / 1672 / 2012, on 2 1107 / 836 /
+// 904. The events are kept until the process ends.
 constexpr int kParts = 8;
 constexpr int kPartTiles = cluster::kMaxTiles / kParts;
 struct ChipPart {
-  hipEvent_t event = nullptr;   // its own
-  hipEvent_t ended = nullptr;   // end of its last run, a part's event: a run over
-                                // several parts records its first one's
+  hipEvent_t ended = nullptr;   // end of the part's last run; null: it is over
   hipStream_t stream = nullptr;
-  unsigned long long used = 0;  // number of the last run, 0: none
+  unsigned long long used = 0;  // number of that run
 };
-struct ClusterTurn {
+struct Chip {
   std::mutex mu;
   ChipPart part[kParts];
+  hipEvent_t event[kParts] = {};
   unsigned long long runs = 0;
 };
-constexpr int kTurnDevices = 64;
-ClusterTurn g_turn[kTurnDevices];
+constexpr int kChipDevices = 64;
+Chip g_chip[kChipDevices];
 
 int parts_of(int cus) { return std::min(cus / kPartTiles, kParts); }
 int parts_for(const cluster::Plan& p) { return (p.tiles + kPartTiles - 1) / kPartTiles; }
 
-hipError_t launch_in_turn(const cluster::Args& a, int model, int device, int cus,
+// While it lives, calls of this thread are allowed that a capture of another
+// thread would forbid (they do not touch its stream).
+struct CaptureAside {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  CaptureAside() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~CaptureAside() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Marks the parts whose last run is over, of other streams than st.
+void find_free_parts(Chip& c, int parts, hipStream_t st) {
+  CaptureAside aside;
+  for (int k = 0; k < parts; ++k) {
+    const hipEvent_t e = c.part[k].ended;
+    if (!e || c.part[k].stream == st) continue;
+    bool seen = false;
+    for (int q = 0; q < k; ++q) seen = seen || c.part[q].ended == e;
+    if (seen) continue;  // asked, and not over
+    if (hipEventQuery(e) == hipSuccess) {
+      for (int q = k; q < parts; ++q)
+        if (c.part[q].ended == e) c.part[q].ended = nullptr;
+    } else {
+      (void)hipGetLastError();  // (not ready is no error)
+    }
+  }
+}
+
+// hipErrorNotReady: too little of the chip is free, nothing has been enqueued.
+hipError_t launch_on_chip(const cluster::Args& a, int model, int device, int cus,
                           hipStream_t st) {
-  ClusterTurn& t = g_turn[device];
-  std::lock_guard<std::mutex> lock(t.mu);
+  Chip& c = g_chip[device];
+  std::lock_guard<std::mutex> lock(c.mu);
   const int parts = parts_of(cus), n = parts_for(a.plan);
   if (n > parts) return hipErrorInvalidValue;
   ChipPart* order[kParts];
-  for (int k = 0; k < parts; ++k) order[k] = &t.part[k];
-  std::stable_sort(order, order + parts, [st](const ChipPart* x, const ChipPart* y) {
-    const bool mx = x->used && x->stream == st, my = y->used && y->stream == st;
-    return mx != my ? mx : x->used < y->used;
+  const auto own = [st](const ChipPart* p) { return p->ended && p->stream == st; };
+  const auto usable = [&](const ChipPart* p) { return !p->ended || p->stream == st; };
+  for (int k = 0; k < parts; ++k) order[k] = &c.part[k];
+  if (std::count_if(order, order + parts, usable) < n) find_free_parts(c, parts, st);
+  // the stream's own, then free ones (the one not used for longest first)
+  std::stable_sort(order, order + parts, [&](const ChipPart* x, const ChipPart* y) {
+    const int rx = own(x) ? 0 : (usable(x) ? 1 : 2), ry = own(y) ? 0 : (usable(y) ? 1 : 2);
+    return rx != ry ? rx < ry : x->used < y->used;
   });
+  if (!usable(order[n - 1])) return hipErrorNotReady;
   hipError_t e = hipSuccess;
-  if (!order[0]->event) e = hipEventCreateWithFlags(&order[0]->event, hipEventDisableTiming);
   for (int k = 0; k < n && e == hipSuccess; ++k) {
-    bool waited = !order[k]->used;
+    bool waited = !order[k]->ended;
     for (int q = 0; q < k; ++q) waited = waited || order[q]->ended == order[k]->ended;
     if (!waited) e = hipStreamWaitEvent(st, order[k]->ended, 0);
+  }
+  // an event that no other part's last run needs
+  hipEvent_t* ended = nullptr;
+  for (int q = 0; q < kParts && !ended; ++q) {
+    bool needed = false;
+    for (int k = n; k < parts; ++k) needed = needed || (c.event[q] && order[k]->ended == c.event[q]);
+    if (!needed) ended = &c.event[q];
+  }
+  if (e == hipSuccess && !*ended) {
+    CaptureAside aside;
+    e = hipEventCreateWithFlags(ended, hipEventDisableTiming);
   }
   if (e != hipSuccess) return e;
   e = cluster::launch_run(a, model, st);
   if (e != hipSuccess) return e;
   // (without its event the run must be over before the parts are given away)
-  hipEvent_t ended = order[0]->event;
-  if (hipEventRecord(ended, st) != hipSuccess) return hipStreamSynchronize(st);
-  ++t.runs;
+  if (hipEventRecord(*ended, st) != hipSuccess) return hipStreamSynchronize(st);
+  ++c.runs;
   for (int k = 0; k < n; ++k) {
-    order[k]->ended = ended;
+    order[k]->ended = *ended;
     order[k]->stream = st;
-    order[k]->used = t.runs;
+    order[k]->used = c.runs;
   }
   return hipSuccess;
 }
@@ -511,7 +552,7 @@ int fvm_bind(fvm_grid* g, double* w_a, double* w_b, const double* ug, void* scra
         hipDeviceGetAttribute(&g->cus, hipDeviceAttributeMultiprocessorCount, g->device) !=
             hipSuccess)
       return FVM_EDEVICE;
-    if (g->device >= kTurnDevices || parts_of(g->cus) < parts_for(g->plan)) g->device = -1;
+    if (g->device >= kChipDevices || parts_of(g->cus) < parts_for(g->plan)) g->device = -1;
     return dev_err(
         cluster::launch_clear_area(g->scr, cluster::area_words(g->nv, g->plan), g->stream));
   }
@@ -940,26 +981,27 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
   if ((kind == 0 || kind == 3) && !g->speeds_valid) rc = enqueue_cfl(g, nullptr);
   if (rc == FVM_OK) rc = arm_log(g, log, nsteps);
   if (rc) return rc;
-  if (kind == 0 && nsteps > 0 && one_workgroup(g, nsteps)) {
-    double* other = g->other(g->cur);
-    double* last = nsteps % 2 ? other : g->cur;
-    double* prev = nsteps % 2 ? g->cur : other;
-    const StepArgs a = g->step_args(g->cur, other, kDtAdaptive);
-    rc = dev_err(launch_resident_run(a, kernel_model(g->p), last, prev, nsteps, g->stream));
-    if (rc) return rc;
-    g->cur = last;
-    g->speeds_valid = true;
-    return FVM_OK;
-  }
-  if (kind != 2 && nsteps >= kMinChipRun && cluster_ok(g)) {
-    double* other = g->other(g->cur);
-    double* last = nsteps % 2 ? other : g->cur;
+  double* const other = g->other(g->cur);
+  double* const last = nsteps % 2 ? other : g->cur;
+  bool one = kind == 0 && nsteps > 0 && one_workgroup(g, nsteps);
+  if (!one && kind != 2 && nsteps >= kMinChipRun && cluster_ok(g)) {
     cluster::Args a = cluster_args(
         g, kind == 0 ? kDtAdaptive : (kind == 3 ? kDtFixedCheck : kDtArray), nsteps, g->cur, last,
         g->other(last));
     a.dts = dts;
     a.dt_arg = dt;
-    rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
+    const hipError_t e = launch_on_chip(a, g->p.model, g->device, g->cus, g->stream);
+    if (e == hipSuccess) {
+      g->cur = last;
+      g->speeds_valid = true;
+    }
+    if (e != hipErrorNotReady) return dev_err(e);
+    one = kind == 0 && resident_ok(g);
+  }
+  if (one) {
+    const StepArgs a = g->step_args(g->cur, other, kDtAdaptive);
+    rc = dev_err(launch_resident_run(a, kernel_model(g->p), last, g->other(last), nsteps,
+                                     g->stream));
     if (rc) return rc;
     g->cur = last;
     g->speeds_valid = true;
@@ -1036,8 +1078,9 @@ int fvm_run_ckpt(fvm_grid* g, int nsteps, int ckpt_every, double* const* ckpts,
       a.every = ckpt_every;
       a.nsaves = saves;
       for (int q = 0; q < saves; ++q) a.saves[q] = ckpts[s + 1 + q];
-      rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
-      if (rc) return rc;
+      const hipError_t e = launch_on_chip(a, g->p.model, g->device, g->cus, g->stream);
+      if (e == hipErrorNotReady) break;
+      if (e != hipSuccess) return dev_err(e);
       k += steps;
       in = end ? last : ckpts[s + saves];
     }
@@ -1483,9 +1526,9 @@ int fvm_adjoint_run(fvm_grid* g, double* const* ckpts, int ckpt_every, const dou
       a.every = 1;
       a.nsaves = a.nsteps;
       for (int q = 0; q < a.nsaves; ++q) a.saves[q] = seg_buf + static_cast<size_t>(q) * state;
-      const int rc = dev_err(launch_in_turn(a, g->p.model, g->device, g->cus, g->stream));
-      if (rc) return rc;
-      k = k1;
+      const hipError_t e = launch_on_chip(a, g->p.model, g->device, g->cus, g->stream);
+      if (e != hipSuccess && e != hipErrorNotReady) return dev_err(e);
+      if (e == hipSuccess) k = k1;
     }
     for (; k + 1 < k1; ++k) {
       double* out = seg_buf + static_cast<size_t>(k - k0) * state;

@@ -7,12 +7,14 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace {
 std::string g_log;
 int g_device = 0;
 std::vector<int> g_event_device;
+std::vector<bool> g_event_over;  // what was recorded last is over (see calls_finish)
 struct Config {
   unsigned grid[3], block[3];
   size_t shared;
@@ -45,6 +47,7 @@ extern "C" {
 const char* calls_log() { return g_log.c_str(); }
 void calls_clear() { g_log.clear(); }
 void calls_device(int device) { g_device = device; }
+void calls_finish() { g_event_over.assign(g_event_over.size(), true); }  // the GPU is idle
 
 int hipGetDevice(int* d) {
   *d = g_device;
@@ -70,13 +73,23 @@ int hipMemcpyAsync(void*, const void*, size_t, int, void*) { return 0; }
 // events are 1, 2, ..; recording one on another device's stream fails
 int hipEventCreateWithFlags(void** e, unsigned) {
   g_event_device.push_back(g_device);
+  g_event_over.push_back(true);
   *e = reinterpret_cast<void*>(g_event_device.size());
   return 0;
 }
 int hipEventRecord(void* e, void* s) {
   const uintptr_t k = reinterpret_cast<uintptr_t>(e);
   if (k == 0 || k > g_event_device.size() || g_event_device[k - 1] != device_of(s)) return 400;
+  g_event_over[k - 1] = false;
   note("record", k, reinterpret_cast<uintptr_t>(s), 0);
+  return 0;
+}
+int hipEventQuery(void* e) {
+  return g_event_over[reinterpret_cast<uintptr_t>(e) - 1] ? 0 : 600;
+}
+int hipThreadExchangeStreamCaptureMode(int* mode) {
+  static int now = 0;
+  std::swap(*mode, now);
   return 0;
 }
 int hipStreamWaitEvent(void* s, void* e, unsigned) {

@@ -2,8 +2,9 @@
 without a GPU: the library runs in a child process on stand-ins of the HIP calls
 (tests/emu/hip_calls.cpp) that log every launch, event record and wait. Such
 runs wait for all of their workgroups to be resident, so runs that are not
-ordered by events must fit the chip together, whatever the handles of their
-streams say: a handle may name another stream than the one it named before."""
+ordered must fit the chip together, whatever the handles of their streams say (a
+handle may name another stream than the one it named before); and no stream waits
+for another one's work."""
 import json
 import os
 import subprocess
@@ -44,9 +45,11 @@ def stream(name, s):
     return L.fvm_set_stream(grids[name], s)
 def device(d):
     return stub.calls_device(d) and 0
+def finish():
+    return stub.calls_finish() and 0
 for f, *args in json.loads(sys.argv[2]):
     stub.calls_clear()
-    code = globals()[f](*args) if f in ("grid", "run", "ckpt", "back", "stream", "device") else \\
+    code = globals()[f](*args) if f in ("grid", "run", "ckpt", "back", "stream", "device", "finish") else \\
         getattr(L, f)(grids[args[0]], *args[1:])
     log = [q.split() for q in stub.calls_log().decode().splitlines()]
     logs.append([code, [[q[0]] + [int(x) for x in q[1:]] for q in log]])
@@ -77,22 +80,27 @@ def calls(tmp_path_factory):
 
 
 def turns(results):
-    """The runs of one log an action, in order: [(tiles, ordered after)]."""
-    runs, done = [], {}
+    """The runs on the chip of a log an action: [(tiles, the runs that are over
+    before it starts: by the events, or since the GPU was idle)]. A stream waits
+    for events of its own handle only."""
+    runs, done, over, of = [], {}, set(), {}
     for code, log in results:
         assert code == 0, results
-        launches = [q for q in log if q[0] == "launch"]
-        after = set()
-        for what, a, b, _ in log:
-            if what == "wait":
-                after |= done.get(a, set())
-            if what == "record":
-                done[a] = after | {len(runs)}
-        if launches:
-            first = next(i for i, q in enumerate(log) if q[0] == "launch")
-            assert all(q[0] != "wait" for q in log[first:]), log
-            assert log[-1][0] == "record", log
-            runs.append((launches[0][1], after))
+        if log == ["finish"]:
+            over = set(range(len(runs)))
+            continue
+        if not any(q[0] == "record" for q in log):
+            assert all(q[0] in ("graph", "launch") for q in log), log
+            continue
+        after = set(over)
+        first = next(i for i, q in enumerate(log) if q[0] == "launch")
+        for what, a, b, _ in log[:first]:
+            assert what == "wait" and of[a] == b, log
+            after |= done[a]
+        assert [q[0] for q in log[first:]] == ["launch", "launch", "record"], log
+        _, event, stream, _ = log[-1]
+        done[event], of[event] = after | {len(runs)}, stream
+        runs.append((log[first][1], after))
     return runs
 
 
@@ -139,22 +147,49 @@ def test_small_grids_on_many_streams_run_side_by_side(calls):
     assert [r[1] for r in runs] == [set()] * 8 + [{k} for k in range(8)]
 
 
+def test_no_stream_waits_for_another(calls):
+    """A run that finds too little of the chip free makes its steps in launches,
+    and is on the chip again once the other stream's run is over."""
+    kinds = lambda log: [q[0] for q in log]
+    chip = ["launch", "launch", "record"]
+    setup = [("grid", "big", 1024, 1024, 2), ("grid", "other", 300, 300, 3),
+             ("grid", "small", 64, 64, 4), ("grid", "tiny", 48, 48, 5)]
+    got = calls(*setup, ("run", "big"), ("run", "other"), ("ckpt", "other", 9, 3),
+                ("back", "other", 12, 6), ("fvm_run", "tiny", 9, 0), ("finish",), ("run", "small"),
+                ("run", "other"), ("run", "big"), ("finish",), ("run", "big"))[4:]
+    assert all(code == 0 for code, _ in got)
+    logs = [kinds(log) for _, log in got]
+    assert logs[0] == chip
+    assert logs[1] == ["graph"]
+    assert set(logs[2]) == set(logs[3]) == {"launch"}
+    assert logs[4] == ["launch"] * 2 and got[4][1][-1][1] == 1  # (maxima,) one workgroup
+    # "other" takes six eighths of the chip, "small" one
+    assert logs[6] == logs[7] == chip
+    assert logs[8] == ["graph"]
+    assert logs[10] == chip
+
+
 @pytest.mark.parametrize("sizes", [[(1024, 1024), (64, 64), (200, 150), (1024, 1024), (64, 64)],
                                    [(200, 150)] * 6, [(300, 300), (64, 64), (700, 400)],
                                    [(130, 96), (64, 64), (512, 512)]])
 def test_unordered_runs_fit_the_chip_together(calls, sizes):
     """Streams taking runs in turn, each stream a handle of its own or all of
-    them one: by the events alone, never more tiles at once than the chip has
+    them one, the GPU idle now and then: never more tiles at once than the chip has
     CUs."""
     n = len(sizes)
-    order = [(3 * k * k + k) % n for k in range(10)]
+    order = [(3 * k * k + k) % n for k in range(14)]
     for same in (False, True):
         grids = [("grid", str(k), nx, ny, 2 if same else 2 + k) for k, (nx, ny) in enumerate(sizes)]
-        runs = turns(calls(*grids, *[("run", str(k)) for k in order])[n:])
+        acts = []
+        for i, k in enumerate(order):
+            acts += [("run", str(k))] + [("finish",)] * (i % 5 == 4)
+        got = calls(*grids, *acts)[n:]
+        runs = turns([[0, ["finish"]] if a == ("finish",) else r for a, r in zip(acts, got)])
         after = [set(r[1]) for r in runs]
         for a in after:
             for k in list(a):
                 a |= after[k]
+        assert len(runs) == 14 if same else len(runs) >= 3
         assert 0 < width(after, [r[0] for r in runs]) <= 256
 
 

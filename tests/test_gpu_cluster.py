@@ -218,19 +218,22 @@ def test_threads_on_streams_of_one_handle():
     (a, _), W = solvers(1, 1, 300, 200)
     W = torch.from_numpy(W).cuda()
     a.run(20)
-    want = a.state()
-    torch.cuda.synchronize()
+    want = a.current_storage().cpu()
     got = []
 
     def work():
         torch.cuda.set_device(0)
         (s, _), _ = solvers(1, 1, 300, 200)
         torch.cuda.synchronize()
+        # (nothing of torch's own runs on these streams: its allocator takes
+        # streams of equal handles for one)
         with torch.cuda.stream(torch.cuda.ExternalStream(2)):
             for _ in range(10):
                 s.set_state(W)
                 s.run(20)
-            got.append((s.sync(), torch.equal(s.state(), want)))
+            status = s.sync()
+            torch.cuda.synchronize()
+        got.append((status, torch.equal(s.current_storage().cpu(), want)))
 
     threads = [threading.Thread(target=work) for _ in range(4)]
     for t in threads:
