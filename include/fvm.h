@@ -359,10 +359,11 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *    of fvm_adjoint_run on a grid that up to 256 tiles of 62 columns and 300
  *    (advection), 76 (Euler) or 50 (spray) rows cover, e.g. 1024 x 1024 Euler,
  *    run on up to 256 workgroups that exchange their tiles' edges, unless they
- *    are of one or two steps (three, where checkpointed or recomputed), the
- *    caller has chosen a strip shape (fvm_set_tiling, fvm_set_cells_per_lane),
- *    the stream is being captured or the stream is another device's than the
- *    grid's or the current one. Such runs on different streams of a process go
+ *    are of one or two steps of a state of more than 2^17 doubles (of up to three
+ *    steps, where checkpointed or recomputed), the caller has chosen a strip
+ *    shape (fvm_set_tiling, fvm_set_cells_per_lane), the stream is being captured
+ *    or the stream is another device's than the grid's or the current one. Such
+ *    runs on different streams of a process go
  *    on side by side where they fit the chip together, counted in eighths of it
  *    (32 tiles); a run that finds too little of it free of other streams' runs
  *    makes its steps in launches and waits for none. Should the workgroups not

@@ -946,8 +946,8 @@ static cluster::Args cluster_args(const fvm_grid* g, int mode, int nsteps, const
   return a;
 }
 
-// The fewest steps for which a run goes on the chip: start, loads and the last two
-// states' stores cost it 10 to 25 us. us a call, steps / chip: one step of 1024^2
+// The fewest steps for which a run of a state of more than a MB goes on the chip:
+// start, loads and the last two states' stores cost it 10 to 25 us. us a call, steps / chip: one step of 1024^2
 // Euler 28.5 / 47.6, 512^2 21.0 / 31.0, 200 x 150 21.2 / 20.5, of 860 x 900 spray
 // 37.6 / 51.7, of 512^2 advection 21.3 / 26.8; two steps 51.5 / 59.9, 32.4 / 38.1,
 // 22.0 / 25.2, 69.6 / 66.6, 24.1 / 31.8; three 79.6 / 73.4, 50.7 / 45.5, 34.3 / 30.1,
@@ -956,8 +956,15 @@ static cluster::Args cluster_args(const fvm_grid* g, int mode, int nsteps, const
 // steps 65.2 / 76.4, three 89.4 / 92.5, four 113 / 110, 300^2 three 42.3 / 46.2, four
 // 53.7 / 51.6; one step recomputed 141 / 178 in a backward pass of four, three
 // 315 / 323 in one of eight, eight 401 / 394 in one of nine.
+// Smaller states start as fast as a graph does (one step with its dt read back:
+// 130 x 96 Euler 45 us on the chip, 46 to 57 as a graph).
 constexpr int kMinChipRun = 3;
+constexpr long long kSmallState = 1 << 17;  // doubles
 constexpr int kMinChipSteps = 4;
+static bool worth_the_chip(const fvm_grid* g, int nsteps) {
+  return nsteps >= kMinChipRun ||
+         (nsteps > 0 && static_cast<long long>(g->nv) * g->p.nx * g->p.ny <= kSmallState);
+}
 
 // One workgroup is the better place for an adaptive run of this grid, or the
 // only one on the chip that is open to it (a captured stream, a strip shape). Past
@@ -984,7 +991,7 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
   double* const other = g->other(g->cur);
   double* const last = nsteps % 2 ? other : g->cur;
   bool one = kind == 0 && nsteps > 0 && one_workgroup(g, nsteps);
-  if (!one && kind != 2 && nsteps >= kMinChipRun && cluster_ok(g)) {
+  if (!one && kind != 2 && worth_the_chip(g, nsteps) && cluster_ok(g)) {
     cluster::Args a = cluster_args(
         g, kind == 0 ? kDtAdaptive : (kind == 3 ? kDtFixedCheck : kDtArray), nsteps, g->cur, last,
         g->other(last));

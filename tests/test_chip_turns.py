@@ -218,6 +218,10 @@ def test_short_runs_are_step_launches(calls):
     ends = on_chip(*[("ckpt", "a", n, 1) for n in (1, 3, 4, 64, 65, 67, 68)])
     assert ends == [0, 0, 1, 1, 1, 1, 2]
     assert on_chip(*[("ckpt", "a", n, 2) for n in (3, 4, 131, 132)]) == [0, 1, 1, 2]
+    # states of up to 2^17 doubles start as fast there as a graph does
+    small = [("grid", "b", 256, 128), ("run", "b", 1), ("run", "b", 2), ("grid", "c", 256, 129),
+             ("run", "c", 2), ("run", "c", 3)]
+    assert on_chip(*small) == [0, 1, 1, 0, 0, 1]
     # segments of so many steps, the first recomputed from its checkpoint
     assert on_chip(("back", "a", 8, 2), ("back", "a", 8, 4), ("back", "a", 10, 5)) == [0, 0, 2]
 
