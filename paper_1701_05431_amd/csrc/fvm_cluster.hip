@@ -662,7 +662,9 @@ hipError_t launch_run(const Args& a, int model, hipStream_t st) {
     h = general_fn<Spray>(bc);
   }
   if (!f) return hipErrorInvalidValue;
-  // every state of the run by tickets has a buffer, the first another than win
+  // every state of the run by tickets has a buffer, the first another than win and
+  // the last but one w_prev, where that is asked for
+  if (a.w_prev && (a.w_prev != a.spare || a.every > 0)) return hipErrorInvalidValue;
   if (!a.w_last ? a.every != 1 || a.nsaves < a.nsteps : a.win == state_buffer(a, 1))
     return hipErrorInvalidValue;
   Args copy = a;
