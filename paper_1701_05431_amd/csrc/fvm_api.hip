@@ -909,6 +909,12 @@ static bool resident_ok(const fvm_grid* g) {
   return need <= kResidentDoubles;
 }
 
+// The stream is being captured, or may be.
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
 // A run of steps can keep the state in the LDS of all CUs: the grid fits, no
 // halo rows, the caller has not asked for a strip shape, the stream is one of the
 // grid's device, which is the current one (the turns' events are its own), and
@@ -921,8 +927,7 @@ static bool cluster_ok(const fvm_grid* g) {
   if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(g->stream, &sdev) != hipSuccess ||
       dev != g->device || sdev != g->device)
     return false;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(g->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  return !capturing(g->stream);
 }
 
 // nsteps steps from state `win` kept on the chip: the last state goes to
@@ -1015,6 +1020,18 @@ static int run_steps(fvm_grid* g, int kind, int nsteps, const double* dts, doubl
     return FVM_OK;
   }
   int done = 0;
+  if (capturing(g->stream)) {  // a graph launched into a capture is not recorded: its steps are
+    for (; done < nsteps; ++done) {
+      StepArgs a = g->step_args(g->cur, g->other(g->cur),
+                                kind == 0 ? kDtAdaptive : (kind == 3 ? kDtFixedCheck : kDtArray));
+      a.dts = dts;
+      a.k = done;
+      a.dt_arg = dt;
+      rc = enqueue_step(g, a);
+      if (rc) return rc;
+      g->cur = a.wout;
+    }
+  }
   while (done < nsteps) {
     hipGraphExec_t exec;
     int n;

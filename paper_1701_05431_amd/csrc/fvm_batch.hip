@@ -360,6 +360,48 @@ struct fvm_batch {
   }
 };
 
+// The launches of nsteps steps from buffer `start`, each through add(kernel,
+// grid, block, argument), which may fail. kind 0: one launch a step; 1: one per
+// grid; 2: kind 0's dry run.
+template <class Add>
+static bool batch_steps(fvm_batch* b, int kind, int nsteps, const double* start, Add&& add) {
+  const double* in = start;
+  bool ok = true;
+  for (int s = 0; s < nsteps && ok; ++s) {
+    double* out = b->other(in);
+    if (kind != 1) {  // 0: persistent launch; 2: its dry run (dt scaled to 0)
+      BatchArgs a = b->args(in, out);
+      a.dt_scale = kind == 2 ? 0.0 : 1.0;
+      ok = add(batch_kernel_ptr(b->model, b->bc, b->wpb, b->persist, b->narrow),
+               dim3(b->persist ? std::min(b->nblocks, b->nitems) : b->nitems),
+               dim3(b->wpb * kWave), &a);
+    } else {
+      for (int q = 0; q < b->n && ok; ++q) {
+        const BatchGrid& r = b->recs[q];
+        StepArgs a{};
+        a.win = in + r.offset;
+        a.wout = out + r.offset;
+        a.scr = b->gscr() + r.user;
+        a.mode = kDtAdaptive;
+        a.g = r.g;
+        // the single-grid kernel's workgroup tiles
+        a.t.rows = r.rows;
+        a.t.wpb = b->wpb;
+        a.t.cpl = r.cpl;
+        a.t.tiles_x = (r.strips_x + b->wpb - 1) / b->wpb;
+        a.t.tiles_y = r.tiles_y;
+        a.t.ntiles = a.t.tiles_x * a.t.tiles_y;
+        a.m = b->m;
+        ok = add(step_kernel_ptr(b->model, b->bc, b->wpb, r.cpl, false), dim3(a.t.ntiles),
+                 dim3(b->wpb * kWave),
+                 &a);
+      }
+    }
+    in = out;
+  }
+  return ok;
+}
+
 extern "C" {
 
 int fvm_batch_create(int n, const fvm_params* p, const size_t* offsets, fvm_batch** out) {
@@ -553,7 +595,6 @@ static int build_batch_graph(fvm_batch* b, int kind, int nsteps, const double* s
   c.cpl_max = b->cpl_max;
   if (hipGraphCreate(&c.graph, 0) != hipSuccess) return FVM_EDEVICE;
   hipGraphNode_t prev = nullptr;
-  const double* in = start;
   auto add = [&](void* fn, dim3 grid, dim3 block, void* arg) -> bool {
     void* kp[] = {arg};
     hipKernelNodeParams np{};
@@ -570,39 +611,7 @@ static int build_batch_graph(fvm_batch* b, int kind, int nsteps, const double* s
     prev = node;
     return true;
   };
-  bool ok = true;
-  for (int s = 0; s < nsteps && ok; ++s) {
-    double* out = b->other(in);
-    if (kind != 1) {  // 0: persistent launch; 2: its dry run (dt scaled to 0)
-      BatchArgs a = b->args(in, out);
-      a.dt_scale = kind == 2 ? 0.0 : 1.0;
-      ok = add(batch_kernel_ptr(b->model, b->bc, b->wpb, b->persist, b->narrow),
-               dim3(b->persist ? std::min(b->nblocks, b->nitems) : b->nitems),
-               dim3(b->wpb * kWave), &a);
-    } else {
-      for (int q = 0; q < b->n && ok; ++q) {
-        const BatchGrid& r = b->recs[q];
-        StepArgs a{};
-        a.win = in + r.offset;
-        a.wout = out + r.offset;
-        a.scr = b->gscr() + r.user;
-        a.mode = kDtAdaptive;
-        a.g = r.g;
-        // the single-grid kernel's workgroup tiles
-        a.t.rows = r.rows;
-        a.t.wpb = b->wpb;
-        a.t.cpl = r.cpl;
-        a.t.tiles_x = (r.strips_x + b->wpb - 1) / b->wpb;
-        a.t.tiles_y = r.tiles_y;
-        a.t.ntiles = a.t.tiles_x * a.t.tiles_y;
-        a.m = b->m;
-        ok = add(step_kernel_ptr(b->model, b->bc, b->wpb, r.cpl, false), dim3(a.t.ntiles),
-                 dim3(b->wpb * kWave),
-                 &a);
-      }
-    }
-    in = out;
-  }
+  const bool ok = batch_steps(b, kind, nsteps, start, add);
   if (!ok || hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0) != hipSuccess) {
     (void)hipGraphDestroy(c.graph);
     return FVM_EDEVICE;
@@ -652,6 +661,17 @@ static int batch_run(fvm_batch* b, int kind, int nsteps, double* log) {
   if (!b->speeds_valid) rc = fvm_batch_cfl(b);
   if (rc == FVM_OK) rc = arm_batch_log(b, log, nsteps);
   if (rc) return rc;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(b->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    // a graph launched into a capture is not recorded: its launches are
+    auto add = [&](void* fn, dim3 grid, dim3 block, void* arg) -> bool {
+      void* kp[] = {arg};
+      return hipLaunchKernel(fn, grid, block, kp, 0, b->stream) == hipSuccess;
+    };
+    if (!batch_steps(b, kind, nsteps, b->cur, add)) return FVM_EDEVICE;
+    if (nsteps % 2) b->cur = b->other(b->cur);
+    return FVM_OK;
+  }
   int done = 0;
   while (done < nsteps) {
     const int left = nsteps - done;
