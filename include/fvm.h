@@ -362,9 +362,9 @@ int fvm_get_cells_per_lane(const fvm_grid* g);
  *    are of one or two steps of a state of more than 2^17 doubles (of up to three
  *    steps, where checkpointed or recomputed), the caller has chosen a strip
  *    shape (fvm_set_tiling, fvm_set_cells_per_lane), the stream is being captured
- *    (the capture then holds each step's launch) or the stream is another device's than the grid's or the current one. Such
- *    runs on different streams of a process go
- *    on side by side where they fit the chip together, counted in eighths of it
+ *    (the capture then holds each step's launch) or the stream is another
+ *    device's than the grid's or the current one. Such runs on different streams
+ *    of a process go on side by side where they fit the chip together, counted in eighths of it
  *    (32 tiles); a run that finds too little of it free of other streams' runs
  *    makes its steps in launches and waits for none. Should the workgroups not
  *    all become resident within 20 ms (another process's kernels, or long ones of
